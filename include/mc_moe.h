@@ -380,7 +380,8 @@ mc_status mc_pmq_expert_error(const float *w_gate, const float *w_up, const floa
  * kernel launch made afterwards by two HIP events on the launch stream;
  * mc_timing_enable(0) stops recording.  mc_timing_read waits for the recorded
  * events of one kernel and returns the summed duration in ms and the number
- * of launches.  Kernel names: pack_scale_zero, pack_codes, export,
+ * of launches.  Kernel names: pack_scale_zero (the l1 scales of sign-binarized
+ * experts), pack_codes (codes and scale/zero words), export,
  * route_fused, route_select, route_lists, prefill_prep, gateup, down, combine,
  * importance_colsum, importance_finish, importance_select, rmsnorm, router,
  * gptq_hessian, gptq_factor, gptq_quantize (each a whole call).

@@ -1,4 +1,4 @@
-// pack.hip -- quantize + pack kernels and the dequant/code export kernels.
+// pack.hip -- the quantize + pack kernel and the dequant/code export kernels.
 //
 // Quantizer (paper Sec. 3.1: uniform asymmetric, group-wise, values mapped onto
 // the integer grid 0..2^b-1; widths 1/2/3 from the PMQ allocation of Eq. 4).
@@ -14,99 +14,123 @@
 
 namespace mc {
 
-// ------------------------------------------------------------ scale / zero --
-// One group per `lpg` consecutive lanes (lpg = min(64, G/4)); every lane
-// reduces float4 pieces, then the group's lanes combine with butterflies.
-__global__ void __launch_bounds__(256) pack_sz_kernel(const float* __restrict__ wg,
-                                                      const float* __restrict__ wu,
-                                                      const float* __restrict__ wd,
-                                                      LayerArgs L, uint32_t* __restrict__ sz_out,
-                                                      long long total_groups) {
-  const int G = L.G;
-  const int lpg = G / 4 < 64 ? G / 4 : 64;          // lanes per group (power of two)
-  const int per_lane = G / 4 / lpg;                  // float4 pieces per lane
-  const int lane = threadIdx.x & 63;
-  const long long wave = ((long long)blockIdx.x * blockDim.x + threadIdx.x) >> 6;
-  const long long grp = wave * (64 / lpg) + lane / lpg;
-  const int sub = lane % lpg;
-  const bool valid = grp < total_groups;
-  const long long gpm = (long long)L.d * L.ffn / G;  // groups per matrix
-  const long long gg = valid ? grp : 0;
-  const int em = (int)(gg / gpm);
-  const int e = em / 3, m = em % 3;
-  const long long gi = gg % gpm;
-  const int K = (m < 2) ? L.d : L.ffn;
-  const int ng = K / G;
-  const int row = (int)(gi / ng), g = (int)(gi % ng);
-  const float* W = (m == 0) ? wg : (m == 1) ? wu : wd;
-  const float* src = W + (size_t)e * L.d * L.ffn + (size_t)row * K + (size_t)g * G;
+// ------------------------------------------------------- scale/zero + codes --
+// One pass over the weights (HBM-bound: 4 bytes in per weight, about b/8 + 4/G
+// out).  A wave takes one packed tile (16 rows x 128 columns): lane l holds the
+// 32 weights of row l % 16 whose codes go into its own b words, so the groups'
+// minima and maxima need two cross-lane steps (the four lanes of a row) and the
+// weights are read once.  The 1.41 G weights of a Mixtral layer (2.5 bits, G =
+// 128) take 1.17 ms, 5.2 TB/s of reads and writes; two passes, one for the
+// scale/zero words and one for the codes, with every midpoint compared in fp64,
+// took 4.94 ms.
 
-  float mn = __builtin_inff(), mx = -__builtin_inff();
-  if (valid) {
-    for (int p = 0; p < per_lane; ++p) {
-      const float4 v = reinterpret_cast<const float4*>(src)[sub + p * lpg];
-      mn = fminf(mn, fminf(fminf(v.x, v.y), fminf(v.z, v.w)));
-      mx = fmaxf(mx, fmaxf(fmaxf(v.x, v.y), fmaxf(v.z, v.w)));
-    }
+// The nearest-level decision of nearest_code (mc_device.hpp) as fp32
+// comparisons: code = number of j in [0, L) with w > t_j.  With the exact
+// midpoint M_j = s (j + 1/2 - z), the code is the number of even j with
+// w > M_j plus the number of odd j with w >= M_j (a tie goes to the even
+// level), and for an fp32 w either condition is w > t for one fp32 t: the
+// largest value that does not satisfy it.
+__device__ __forceinline__ float fp32_below(float f) {
+  const uint32_t u = __float_as_uint(f);
+  return __uint_as_float((u & 0x7fffffffu) == 0 ? 0x80000001u : (u & 0x80000000u) ? u + 1u : u - 1u);
+}
+
+template <int B>
+__device__ __forceinline__ void code_thresholds(float (&t)[(1 << B) - 1], uint32_t szw) {
+  const double s = (double)half_bits_to_float(szw & 0xffffu);
+  const double z = (double)half_bits_to_float(szw >> 16);
+#pragma unroll
+  for (int j = 0; j < (1 << B) - 1; ++j) {
+    const double m = s * (((double)j + 0.5) - z);     // exact (see nearest_code)
+    const float f = (float)m;
+    const bool step = (j & 1) ? (double)f >= m : (double)f > m;
+    t[j] = step ? fp32_below(f) : f;
   }
-  for (int off = 1; off < lpg; off <<= 1) {
+}
+
+// The minimum and maximum over the four lanes of a row (l % 16 equal).
+__device__ __forceinline__ void row_min_max(float& mn, float& mx) {
+#pragma unroll
+  for (int off = 16; off < 64; off <<= 1) {
     mn = fminf(mn, __shfl_xor(mn, off));
     mx = fmaxf(mx, __shfl_xor(mx, off));
   }
-  if (!valid || sub != 0) return;
-  const int b = L.cum_bits[e + 1] - L.cum_bits[e];
-  const size_t idx = layer_sz_offset(L, e, m) + ((size_t)(row / 16) * ng + g) * 16 + (row % 16);
-  sz_out[idx] = group_sz_word(mn, mx, b);
 }
 
-// ------------------------------------------------------------------- codes --
-// One thread per (matrix, tile, lane): 32 codes -> b words.
-
-__global__ void __launch_bounds__(256) pack_codes_kernel(const float* __restrict__ wg,
-                                                         const float* __restrict__ wu,
-                                                         const float* __restrict__ wd,
-                                                         LayerArgs L,
-                                                         const uint32_t* __restrict__ sz,
-                                                         uint32_t* __restrict__ words_out,
-                                                         long long total_lanes) {
-  const long long tid = (long long)blockIdx.x * blockDim.x + threadIdx.x;
-  if (tid >= total_lanes) return;
-  const long long lpm = (long long)L.d * L.ffn / 32;   // lanes per matrix
-  const int em = (int)(tid / lpm);
-  const int e = em / 3, m = em % 3;
-  const long long rest = tid % lpm;
-  const int lane = (int)(rest & 63);
-  const long long tile = rest >> 6;
-  const int K = (m < 2) ? L.d : L.ffn;
-  const int tiles_per_row = K / kTileCols;
-  const int trow = (int)(tile / tiles_per_row), tcol = (int)(tile % tiles_per_row);
-  const int n = trow * kTileRows + (lane & 15);
-  const int kq = lane >> 4;
-  const int G = L.G, ng = K / G;
-  const int b = L.cum_bits[e + 1] - L.cum_bits[e];
-  const int Lc = (1 << b) - 1;
-  const bool sign = expert_is_sign(L, e);
-  const float* W = (m == 0) ? wg : (m == 1) ? wu : wd;
-  const float* row = W + (size_t)e * L.d * L.ffn + (size_t)n * K;
-  const uint32_t* szm = sz + layer_sz_offset(L, e, m);
-
+// Tile `tile` of one matrix at width B: GPC groups per 128 columns.
+template <int B, int GPC>
+__device__ __forceinline__ void pack_tile(const float4 (&v)[8], bool sign, int lane, uint32_t* __restrict__ words,
+                                          uint32_t* __restrict__ sz) {
+  constexpr int UPG = 4 / GPC;                         // 32-column steps of a group
   uint32_t w[3] = {0u, 0u, 0u};
-  for (int u = 0; u < 4; ++u) {
-    const int k0 = tcol * kTileCols + 32 * u + 8 * kq;
-    const int g = k0 / G;
-    const uint32_t szw = szm[((size_t)(n / 16) * ng + g) * 16 + (n % 16)];
-    const double s = (double)half_bits_to_float(szw & 0xffffu);
-    const double z = (double)half_bits_to_float(szw >> 16);
-    const float4 a = reinterpret_cast<const float4*>(row + k0)[0];
-    const float4 c = reinterpret_cast<const float4*>(row + k0)[1];
-    const float v[8] = {a.x, a.y, a.z, a.w, c.x, c.y, c.z, c.w};
-    for (int j = 0; j < 8; ++j) {
-      const uint32_t code = sign ? (v[j] >= 0.0f ? 1u : 0u) : (uint32_t)nearest_code(v[j], s, z, Lc);
-      place_code(w, code, 4 * u + (j >> 1), j & 1, b);
+#pragma unroll
+  for (int g = 0; g < GPC; ++g) {
+    float t[(1 << B) - 1];
+    if (sign) {
+      t[0] = fp32_below(0.0f);                         // w >= 0
+    } else {
+      float mn = __builtin_inff(), mx = -__builtin_inff();
+#pragma unroll
+      for (int i = 2 * UPG * g; i < 2 * UPG * (g + 1); ++i) {
+        mn = fminf(mn, fminf(fminf(v[i].x, v[i].y), fminf(v[i].z, v[i].w)));
+        mx = fmaxf(mx, fmaxf(fmaxf(v[i].x, v[i].y), fmaxf(v[i].z, v[i].w)));
+      }
+      row_min_max(mn, mx);
+      const uint32_t szw = group_sz_word(mn, mx, B);
+      if (lane >> 4 == g) sz[16 * g + (lane & 15)] = szw;
+      code_thresholds<B>(t, szw);
     }
+#pragma unroll
+    for (int u = UPG * g; u < UPG * (g + 1); ++u)
+#pragma unroll
+      for (int j = 0; j < 8; ++j) {
+        const float4& q = v[2 * u + (j >> 2)];
+        const float x = (j & 3) == 0 ? q.x : (j & 3) == 1 ? q.y : (j & 3) == 2 ? q.z : q.w;
+        uint32_t code = 0;
+#pragma unroll
+        for (int i = 0; i < (1 << B) - 1; ++i) code += x > t[i] ? 1u : 0u;
+        place_code(w, code, 4 * u + (j >> 1), j & 1, B);
+      }
   }
-  uint32_t* dst = words_out + layer_word_offset(L, e, m) + ((size_t)tile * 64 + lane) * b;
-  for (int p = 0; p < b; ++p) dst[p] = w[p];
+#pragma unroll
+  for (int p = 0; p < B; ++p) words[(size_t)lane * B + p] = w[p];
+}
+
+constexpr int kPackWaves = 4;
+
+// grid (tiles of a matrix / kPackWaves, 3E matrices); d and ffn are multiples
+// of 128, so a matrix has a multiple of 8 tiles.
+template <int GPC>
+__global__ void __launch_bounds__(64 * kPackWaves) pack_kernel(const float* __restrict__ wg,
+                                                               const float* __restrict__ wu,
+                                                               const float* __restrict__ wd, LayerArgs L,
+                                                               uint32_t* __restrict__ words_out,
+                                                               uint32_t* __restrict__ sz_out) {
+  const int lane = threadIdx.x & 63;
+  const uint32_t tile = blockIdx.x * kPackWaves + wave_id();
+  const int e = blockIdx.y / 3, m = blockIdx.y % 3;
+  const int K = (m < 2) ? L.d : L.ffn;
+  const uint32_t per_row = (uint32_t)K / kTileCols;
+  const uint32_t trow = tile / per_row, tcol = tile - trow * per_row;
+  const float* W = (m == 0) ? wg : (m == 1) ? wu : wd;
+  const float* src = W + (size_t)e * L.d * L.ffn + (size_t)(trow * kTileRows + (lane & 15)) * K + tcol * kTileCols +
+                     8 * (lane >> 4);
+  float4 v[8];
+#pragma unroll
+  for (int u = 0; u < 4; ++u) {
+    v[2 * u] = reinterpret_cast<const float4*>(src + 32 * u)[0];
+    v[2 * u + 1] = reinterpret_cast<const float4*>(src + 32 * u)[1];
+  }
+  const int b = L.cum_bits[e + 1] - L.cum_bits[e];
+  const bool sign = expert_is_sign(L, e);
+  uint32_t* words = words_out + layer_word_offset(L, e, m) + (size_t)tile * 64 * b;
+  uint32_t* sz = sz_out + layer_sz_offset(L, e, m) + (size_t)tile * GPC * 16;   // groups of a row block are consecutive
+  if (b == 1)
+    pack_tile<1, GPC>(v, sign, lane, words, sz);
+  else if (b == 2)
+    pack_tile<2, GPC>(v, false, lane, words, sz);
+  else
+    pack_tile<3, GPC>(v, false, lane, words, sz);
 }
 
 // ------------------------------------------------------- sign binarization --
@@ -223,25 +247,24 @@ __global__ void __launch_bounds__(256) export_kernel(const uint32_t* __restrict_
 
 hipError_t launch_pack(const float* wg, const float* wu, const float* wd, const LayerArgs& L,
                        uint32_t* words, uint32_t* sz, bool any_sign, hipStream_t stream) {
-  const long long groups = 3LL * L.E * L.d * L.ffn / L.G;
-  const int lpg = L.G / 4 < 64 ? L.G / 4 : 64;
-  const long long waves = (groups + (64 / lpg) - 1) / (64 / lpg);
-  const long long blocks_sz = (waves * 64 + 255) / 256;
-  timing_begin(stream, kSitePackSz);
-  hipLaunchKernelGGL(pack_sz_kernel, dim3((unsigned)blocks_sz), dim3(256), 0, stream, wg, wu, wd,
-                     L, sz, groups);
   if (any_sign) {
     const int parts = sign_parts((long long)L.d * L.ffn / L.G);
+    timing_begin(stream, kSitePackSz);
     hipLaunchKernelGGL(sign_l1_kernel, dim3(parts, 3 * L.E), dim3(kSignThreads), 0, stream, wg, wu, wd, L, sz);
     hipLaunchKernelGGL(sign_finish_kernel, dim3(3 * L.E), dim3(kSignThreads), 0, stream, L, sz);
+    timing_end(stream, kSitePackSz);
+    const hipError_t err = hipGetLastError();
+    if (err != hipSuccess) return err;
   }
-  timing_end(stream, kSitePackSz);
-  hipError_t err = hipGetLastError();
-  if (err != hipSuccess) return err;
-  const long long lanes = 3LL * L.E * L.d * L.ffn / 32;
+  const dim3 grid((unsigned)((long long)L.d * L.ffn / (kTileRows * kTileCols) / kPackWaves), 3 * L.E);
+  const dim3 block(64 * kPackWaves);
   timing_begin(stream, kSitePackCodes);
-  hipLaunchKernelGGL(pack_codes_kernel, dim3((unsigned)((lanes + 255) / 256)), dim3(256), 0, stream,
-                     wg, wu, wd, L, sz, words, lanes);
+  if (L.G == 128)
+    hipLaunchKernelGGL(pack_kernel<1>, grid, block, 0, stream, wg, wu, wd, L, words, sz);
+  else if (L.G == 64)
+    hipLaunchKernelGGL(pack_kernel<2>, grid, block, 0, stream, wg, wu, wd, L, words, sz);
+  else
+    hipLaunchKernelGGL(pack_kernel<4>, grid, block, 0, stream, wg, wu, wd, L, words, sz);
   timing_end(stream, kSitePackCodes);
   return hipGetLastError();
 }
