@@ -187,16 +187,22 @@ static int decode_splits(int K, int* c_per) {
   return S;
 }
 
-// Splits of the down reduction: the decode GEMV's, or the prefill GEMM's.
-int forward_nsplit(int T, int E, int k, int d, int ffn) {
-  if (T > kDecodeMaxT) return prefill_layout(T, E, k, d, ffn).nsplit;
-  return decode_splits(ffn, nullptr);
-}
-
-// Splits of the decode gate/up reduction over d (1 up to d = 4352).
-int forward_ksplit(int T, int E, int k, int d, int ffn) {
-  (void)T; (void)E; (void)k; (void)ffn;
-  return decode_splits(d, nullptr);
+// Whether a batch takes the decode GEMVs (else the grouped GEMMs of the
+// prefill path).  Up to kDecodeMaxT tokens the GEMVs stream the weights
+// faster, but once per 16 pairs of an expert, and every piece of a matrix
+// costs a workgroup a set-up; the GEMMs stream them once per 32 pairs and pay
+// one more launch.  So the GEMMs take batches with 12 or more pairs an expert
+// (Mixtral layer at 32 tokens: GEMVs 124 us, GEMMs 136; 48: 143 and 146; 64:
+// 167 and 151), and from 12 tokens on the layers whose touched experts are
+// small (OLMoE layer, 403 M weights, at 16 tokens: 47.9 and 46.1 us, 32: 55 and
+// 49; 16 experts of 11 M weights, 16 tokens: 49 and 40; 60 of 21.5 M, 16
+// tokens: 61 and 68).  A small batch whose GEMM workspace would not fit the
+// library's own scratch keeps the GEMVs.
+static bool use_decode(int T, int E, int k, int d, int ffn) {
+  if (T > kDecodeMaxT) return false;
+  const double touched = (double)(T * k < E ? T * k : E) * 3.0 * d * ffn;
+  const bool gemm = (double)T * k >= 12.0 * E || (T >= 12 && touched <= 450e6);
+  return !gemm || prefill_workspace_bytes(T, E, k, d, ffn) > MC_NOALLOC_SCRATCH_BYTES;
 }
 
 // Compute units of the current device (one decode workgroup each).
@@ -217,12 +223,12 @@ static int device_cus() {
 static size_t round256(size_t b) { return ((b + 255) / 256) * 256; }
 
 size_t forward_workspace_bytes(int T, int E, int k, int d, int ffn) {
-  if (T > kDecodeMaxT) return prefill_layout(T, E, k, d, ffn).total;
+  if (!use_decode(T, E, k, d, ffn)) return prefill_workspace_bytes(T, E, k, d, ffn);
   const size_t P = (size_t)T * k;
-  const int ks = forward_ksplit(T, E, k, d, ffn);
+  const int ks = decode_splits(d, nullptr);
   const size_t h = round256(P * ffn * sizeof(uint16_t));
   const size_t gu = ks > 1 ? round256((size_t)ks * 2 * P * ffn * sizeof(float)) : 0;
-  const size_t part = (size_t)forward_nsplit(T, E, k, d, ffn) * P * d * sizeof(float);
+  const size_t part = (size_t)decode_splits(ffn, nullptr) * P * d * sizeof(float);
   return h + gu + part;
 }
 
@@ -294,7 +300,8 @@ hipError_t launch_expert_partials(const uint16_t* x, const LayerArgs& L, const m
                                   float** partial_out, size_t* part_stride_out, int* nsplit_out,
                                   hipStream_t stream) {
   const int T = r.T, k = r.k;
-  if (T > kDecodeMaxT) return launch_prefill(x, L, r, ws, partial_out, part_stride_out, nsplit_out, stream);
+  if (!use_decode(T, r.E, k, L.d, L.ffn))
+    return launch_prefill(x, L, r, ws, partial_out, part_stride_out, nsplit_out, stream);
   const size_t P = (size_t)T * k;
   DecodeArgs a;
   a.x = x;

@@ -6,7 +6,7 @@
 namespace mc {
 
 constexpr int kRouteFusedMaxT = 64;    // up to this many tokens routing may run in one launch
-constexpr int kDecodeMaxT = 64;        // up to this many tokens one workgroup holds all of an expert's tokens
+constexpr int kDecodeMaxT = 64;        // the decode GEMVs take at most this many tokens
 
 enum TimingSite {
   kSitePackSz, kSitePackCodes, kSiteExport, kSiteRouteFused, kSiteRouteSelect, kSiteRouteLists,
@@ -52,8 +52,6 @@ hipError_t launch_route_batch(const float* logits, const uint8_t* important, flo
 // and the set laid out at base.
 size_t routing_set_bytes(int T, int E, int k);
 mc_routing routing_set(void* base, int T, int E, int k);
-int forward_nsplit(int T, int E, int k, int d, int ffn);
-int forward_ksplit(int T, int E, int k, int d, int ffn);
 size_t forward_workspace_bytes(int T, int E, int k, int d, int ffn);
 // Workspace of the prefill path (byte offsets): expert tile tables, the
 // fragment-tiled copies of the routed x rows (bf16) and of h (fp16) with their
@@ -61,8 +59,10 @@ size_t forward_workspace_bytes(int T, int E, int k, int d, int ffn);
 struct PrefillLayout {
   size_t tables, x, xsum, h, hsum, part, total;
   int f_max, mt_max, nsplit;
+  int tiles;               // fragment rows (32 tokens) per m-tile: 1, 2 or 4
 };
-PrefillLayout prefill_layout(int T, int E, int k, int d, int ffn);
+PrefillLayout prefill_layout(int T, int E, int k, int d, int ffn, int G);
+size_t prefill_workspace_bytes(int T, int E, int k, int d, int ffn);
 hipError_t launch_prefill(const uint16_t* x, const LayerArgs& L, const mc_routing& r, void* ws,
                           float** partial, size_t* part_stride, int* nsplit, hipStream_t stream);
 // Routing inputs of a forward call that routes its batch first (the outputs

@@ -3,19 +3,20 @@
 // and their launcher.  The GEMM kernels are in prefill.hpp, one file per
 // group size.
 #include "prefill.hpp"
+#include <algorithm>
 
 namespace mc {
 
 extern template hipError_t launch_prefill_gemm<1>(const LayerArgs&, const int32_t*, const PrefillTables&,
-                                                  const PrefillGemm&, bool, hipStream_t);
+                                                  const PrefillGemm&, bool, int, hipStream_t);
 extern template hipError_t launch_prefill_gemm<2>(const LayerArgs&, const int32_t*, const PrefillTables&,
-                                                  const PrefillGemm&, bool, hipStream_t);
+                                                  const PrefillGemm&, bool, int, hipStream_t);
 extern template hipError_t launch_prefill_gemm<4>(const LayerArgs&, const int32_t*, const PrefillTables&,
-                                                  const PrefillGemm&, bool, hipStream_t);
+                                                  const PrefillGemm&, bool, int, hipStream_t);
 
 // The prefill's preparation, one workgroup per fragment row f (f_max of
 // them).  Every workgroup first scans the expert counts itself (thread e:
-// fragment rows ceil(M_e/32) and m-tiles of PfCfg::kTokens tokens; wave
+// fragment rows ceil(M_e/32) and m-tiles of tb.tiles fragment rows; wave
 // prefix sums), which gives the expert that f belongs to; workgroup 0 also
 // writes the tables the GEMMs read.  Counts outside [0, P] are taken as 0,
 // and tables that would not fit their capacity are left empty (no m-tiles,
@@ -51,7 +52,7 @@ __global__ void __launch_bounds__(kGatherThreads) prefill_prep_kernel(const uint
   // tables: exclusive prefix sums of the experts' fragment rows and m-tiles
   const int c = tid < E ? checked_count(counts[tid], tb.P) : 0;
   const int nf = (c + kPfFragRows - 1) / kPfFragRows;
-  const int nm = (c + PfCfg::kTokens - 1) / PfCfg::kTokens;
+  const int nm = (nf + tb.tiles - 1) / tb.tiles;
   int sf = nf, sm = nm;
   for (int off = 1; off < 64; off <<= 1) {
     const int a = __shfl_up(sf, off), b = __shfl_up(sm, off);
@@ -75,7 +76,7 @@ __global__ void __launch_bounds__(kGatherThreads) prefill_prep_kernel(const uint
     tm += wm[w];
   }
   const bool fits = tf <= tb.f_max && tm <= tb.mt_max;
-  if (f == 0) {
+  if (f == 0 && blockIdx.y == 0) {
     if (!fits) {
       for (int i = tid; i <= E; i += kGatherThreads) tb.ftile_base[i] = 0;
       if (tid == 0) *tb.mt_count = 0;
@@ -114,7 +115,7 @@ __global__ void __launch_bounds__(kGatherThreads) prefill_prep_kernel(const uint
   }
   const int ng = d / (8 * GP);
   unsigned char* out = reinterpret_cast<unsigned char*>(xt) + frag_offset(f, 0, 0, d);
-  for (int c0 = 0; c0 < d; c0 += kGatherCols) {
+  for (int c0 = blockIdx.y * kGatherCols; c0 < d; c0 += gridDim.y * kGatherCols) {
     const int w = (d - c0) < kGatherCols ? (d - c0) : kGatherCols;   // a multiple of 128
     const bool on = 8 * lane < w;
     u32x4 v[kRowsPerWave];
@@ -123,7 +124,7 @@ __global__ void __launch_bounds__(kGatherThreads) prefill_prep_kernel(const uint
       v[j] = u32x4{0u, 0u, 0u, 0u};
       if (on && src[j]) v[j] = *reinterpret_cast<const u32x4*>(src[j] + c0 + 8 * lane);
     }
-    if (c0 > 0) __syncthreads();   // the previous block's tile has been written out
+    if (c0 >= (int)gridDim.y * kGatherCols) __syncthreads();   // the previous block's tile has been written out
 #pragma unroll
     for (int j = 0; j < kRowsPerWave; ++j) {
       const int m = wave + 4 * j;
@@ -144,24 +145,61 @@ __global__ void __launch_bounds__(kGatherThreads) prefill_prep_kernel(const uint
 
 static size_t round256(size_t b) { return ((b + 255) / 256) * 256; }
 
-PrefillLayout prefill_layout(int T, int E, int k, int d, int ffn) {
+// Fragment rows of the m-tiles, from the pairs an expert sees on average.
+// Measured (us a layer call, m-tiles of 1 / 2 / 4 fragment rows): Mixtral
+// layer (G = 128) at 64 tokens 151 / 160 / 237, 128: 194 / 187 / 267, 333:
+// 355 / 305 / 409, 1200: - / 834 / 890; with G = 64 at 96: 192 / 205 / -, 1024:
+// - / 884 / 921, 4096: - / 3110 / 2930; OLMoE layer (G = 64) at 512 tokens: 120
+// / 125 / 163, 2048: 321 / 316 / 358.  Smaller m-tiles unpack (and read) the
+// weights more often but keep more workgroups on a CU.  From 512 pairs an
+// expert on, the 128-token ones: in a short run the 64-token ones are faster
+// there too (Mixtral, 4096 tokens: 2468 against 2573 us), but under sustained
+// load, where the card's power sets the clock, the extra unpacking costs more
+// than it hides (2889 against 2867).
+static int prefill_tiles(int T, int E, int k) {
+  const double per = (double)T * k / E;
+  return per <= 40 ? 1 : per < 512 ? 2 : 4;
+}
+
+// Weight rows of a workgroup (ffn rows of gate/up, d rows of down).
+template <int GPC>
+static int prefill_rows_g(int tiles, bool gateup) {
+  if (tiles == 1) return gateup ? PfTile<1, GPC>::kRowsGateUp : PfTile<1, GPC>::kRowsDown;
+  if (tiles == 2) return gateup ? PfTile<2, GPC>::kRowsGateUp : PfTile<2, GPC>::kRowsDown;
+  return gateup ? PfTile<4, GPC>::kRowsGateUp : PfTile<4, GPC>::kRowsDown;
+}
+static int prefill_rows(int tiles, int G, bool gateup) {
+  return G == 128 ? prefill_rows_g<1>(tiles, gateup) : G == 64 ? prefill_rows_g<2>(tiles, gateup)
+                                                               : prefill_rows_g<4>(tiles, gateup);
+}
+
+PrefillLayout prefill_layout(int T, int E, int k, int d, int ffn, int G) {
   PrefillLayout pl;
   const size_t P = (size_t)T * k;
   pl.f_max = (int)((P + (size_t)(kPfFragRows - 1) * E) / kPfFragRows);
-  pl.mt_max = (int)((P + (size_t)(PfCfg::kTokens - 1) * E) / PfCfg::kTokens);
-  const int nt_down = (d + PfCfg::kRowsDown - 1) / PfCfg::kRowsDown;
-  // Split the down GEMM's reduction so that its workgroups fill the 256 CUs
-  // in whole rounds: pick s minimising rounds(s) / s (the time of one round
+  pl.tiles = prefill_tiles(T, E, k);
+  const size_t mtok = (size_t)pl.tiles * kPfFragRows;
+  pl.mt_max = (int)((P + (mtok - 1) * E) / mtok);
+  // Split the down GEMM's reduction so that its workgroups fill the CUs in
+  // whole rounds: pick s minimising rounds(s) / s (the time of one round
   // shrinks as 1/s), the smallest on ties; at least 8 chunks per split.
-  const long long wgs = (long long)pl.mt_max * nt_down;
+  const int rows_down = prefill_rows(pl.tiles, G, false);
+  const int nt_down = (d + rows_down - 1) / rows_down;
+  const int slots = 256 * (pl.tiles == 4 ? 1 : pl.tiles == 2 ? (G == 128 ? 2 : 3) : 4);   // workgroups at once
+  long long mt = pl.mt_max;
+  if (pl.tiles < 4) {   // about the m-tiles in use
+    const double per = (double)P / E / mtok;
+    const long long est = (long long)(E * (per < 0.5 ? 1.0 : per + 0.5));
+    if (est < mt) mt = est;
+  }
+  const long long wgs = mt * nt_down;
   int maxs = (ffn / kTileCols) / 8;
   if (maxs > 4) maxs = 4;
   int s = 1;
   for (int c = 2; c <= maxs; ++c)
-    if ((double)((wgs * c + 255) / 256) / c < (double)((wgs * s + 255) / 256) / s - 1e-9) s = c;
-  pl.nsplit = s;
-  // the GEMMs stage whole m-tiles: kTiles - 1 padding fragment rows past the last one
-  const size_t rows = (size_t)(pl.f_max + PfCfg::kTiles) * kPfFragRows;
+    if ((double)((wgs * c + slots - 1) / slots) / c < (double)((wgs * s + slots - 1) / slots) / s - 1e-9) s = c;
+  // the GEMMs stage whole m-tiles: tiles - 1 padding fragment rows past the last one
+  const size_t rows = (size_t)(pl.f_max + pl.tiles) * kPfFragRows;
   pl.tables = 0;
   const size_t tab = (size_t)(E + 1 + 2 * pl.mt_max + 1) * sizeof(int32_t);
   pl.x = round256(tab);
@@ -169,13 +207,24 @@ PrefillLayout prefill_layout(int T, int E, int k, int d, int ffn) {
   pl.h = pl.xsum + round256(rows * (d / 32) * sizeof(float));   // G >= 32
   pl.hsum = pl.h + round256(rows * ffn * sizeof(uint16_t));
   pl.part = pl.hsum + round256(rows * (ffn / 32) * sizeof(float));
-  pl.total = pl.part + (size_t)pl.nsplit * P * d * sizeof(float);
+  // a batch that fits the library's own scratch with fewer splits takes those
+  const size_t split = P * d * sizeof(float);
+  if (pl.part + s * split > MC_NOALLOC_SCRATCH_BYTES && pl.part + split <= MC_NOALLOC_SCRATCH_BYTES)
+    s = (int)((MC_NOALLOC_SCRATCH_BYTES - pl.part) / split);
+  pl.nsplit = s;
+  pl.total = pl.part + (size_t)s * split;
   return pl;
+}
+
+// The workspace query does not name the group size: the largest layout.
+size_t prefill_workspace_bytes(int T, int E, int k, int d, int ffn) {
+  return std::max({prefill_layout(T, E, k, d, ffn, 32).total, prefill_layout(T, E, k, d, ffn, 64).total,
+                   prefill_layout(T, E, k, d, ffn, 128).total});
 }
 
 hipError_t launch_prefill(const uint16_t* x, const LayerArgs& L, const mc_routing& r, void* ws,
                           float** partial, size_t* part_stride, int* nsplit, hipStream_t stream) {
-  const PrefillLayout pl = prefill_layout(r.T, r.E, r.k, L.d, L.ffn);
+  const PrefillLayout pl = prefill_layout(r.T, r.E, r.k, L.d, L.ffn, L.G);
   char* base = static_cast<char*>(ws);
   PrefillTables tb;
   int32_t* t = reinterpret_cast<int32_t*>(base + pl.tables);
@@ -185,6 +234,7 @@ hipError_t launch_prefill(const uint16_t* x, const LayerArgs& L, const mc_routin
   tb.mt_count = tb.mt_j + pl.mt_max;
   tb.f_max = pl.f_max;
   tb.mt_max = pl.mt_max;
+  tb.tiles = pl.tiles;
   tb.T = r.T;
   tb.P = r.T * r.k;
   uint16_t* xt = reinterpret_cast<uint16_t*>(base + pl.x);
@@ -195,15 +245,16 @@ hipError_t launch_prefill(const uint16_t* x, const LayerArgs& L, const mc_routin
   *part_stride = (size_t)r.T * r.k * L.d;
   *nsplit = pl.nsplit;
 
+  const dim3 pgrid(pl.f_max, (L.d + kGatherCols - 1) / kGatherCols);
   timing_begin(stream, kSitePrefillPrep);
   if (L.G == 128)
-    hipLaunchKernelGGL(prefill_prep_kernel<16>, dim3(pl.f_max), dim3(kGatherThreads), 0, stream, x, L.d, r.E,
+    hipLaunchKernelGGL(prefill_prep_kernel<16>, pgrid, dim3(kGatherThreads), 0, stream, x, L.d, r.E,
                        r.counts, r.offsets, r.pair_token, tb, xt, xsum);
   else if (L.G == 64)
-    hipLaunchKernelGGL(prefill_prep_kernel<8>, dim3(pl.f_max), dim3(kGatherThreads), 0, stream, x, L.d, r.E,
+    hipLaunchKernelGGL(prefill_prep_kernel<8>, pgrid, dim3(kGatherThreads), 0, stream, x, L.d, r.E,
                        r.counts, r.offsets, r.pair_token, tb, xt, xsum);
   else
-    hipLaunchKernelGGL(prefill_prep_kernel<4>, dim3(pl.f_max), dim3(kGatherThreads), 0, stream, x, L.d, r.E,
+    hipLaunchKernelGGL(prefill_prep_kernel<4>, pgrid, dim3(kGatherThreads), 0, stream, x, L.d, r.E,
                        r.counts, r.offsets, r.pair_token, tb, xt, xsum);
   timing_end(stream, kSitePrefillPrep);
   hipError_t err = hipGetLastError();
@@ -213,7 +264,7 @@ hipError_t launch_prefill(const uint16_t* x, const LayerArgs& L, const mc_routin
   gu.a = xt;
   gu.asum = xsum;
   gu.K = L.d;
-  gu.n_tiles = L.ffn / PfCfg::kRowsGateUp;
+  gu.n_tiles = L.ffn / prefill_rows(pl.tiles, L.G, true);
   gu.c_per_split = L.d / kTileCols;
   gu.nsplit = 1;
   gu.h = ht;
@@ -221,9 +272,9 @@ hipError_t launch_prefill(const uint16_t* x, const LayerArgs& L, const mc_routin
   gu.partial = nullptr;
   gu.part_stride = 0;
   timing_begin(stream, kSiteGateUp);
-  if (L.G == 128) err = launch_prefill_gemm<1>(L, r.offsets, tb, gu, true, stream);
-  else if (L.G == 64) err = launch_prefill_gemm<2>(L, r.offsets, tb, gu, true, stream);
-  else err = launch_prefill_gemm<4>(L, r.offsets, tb, gu, true, stream);
+  if (L.G == 128) err = launch_prefill_gemm<1>(L, r.offsets, tb, gu, true, pl.tiles, stream);
+  else if (L.G == 64) err = launch_prefill_gemm<2>(L, r.offsets, tb, gu, true, pl.tiles, stream);
+  else err = launch_prefill_gemm<4>(L, r.offsets, tb, gu, true, pl.tiles, stream);
   timing_end(stream, kSiteGateUp);
   if (err != hipSuccess) return err;
 
@@ -232,7 +283,8 @@ hipError_t launch_prefill(const uint16_t* x, const LayerArgs& L, const mc_routin
   dn.a = ht;
   dn.asum = hsum;
   dn.K = L.ffn;
-  dn.n_tiles = (L.d + PfCfg::kRowsDown - 1) / PfCfg::kRowsDown;
+  const int rows_dn = prefill_rows(pl.tiles, L.G, false);
+  dn.n_tiles = (L.d + rows_dn - 1) / rows_dn;
   dn.c_per_split = (ntk + pl.nsplit - 1) / pl.nsplit;
   dn.nsplit = pl.nsplit;
   dn.h = nullptr;
@@ -240,9 +292,9 @@ hipError_t launch_prefill(const uint16_t* x, const LayerArgs& L, const mc_routin
   dn.partial = *partial;
   dn.part_stride = *part_stride;
   timing_begin(stream, kSiteDown);
-  if (L.G == 128) err = launch_prefill_gemm<1>(L, r.offsets, tb, dn, false, stream);
-  else if (L.G == 64) err = launch_prefill_gemm<2>(L, r.offsets, tb, dn, false, stream);
-  else err = launch_prefill_gemm<4>(L, r.offsets, tb, dn, false, stream);
+  if (L.G == 128) err = launch_prefill_gemm<1>(L, r.offsets, tb, dn, false, pl.tiles, stream);
+  else if (L.G == 64) err = launch_prefill_gemm<2>(L, r.offsets, tb, dn, false, pl.tiles, stream);
+  else err = launch_prefill_gemm<4>(L, r.offsets, tb, dn, false, pl.tiles, stream);
   timing_end(stream, kSiteDown);
   return err;
 }

@@ -3,5 +3,5 @@
 
 namespace mc {
 template hipError_t launch_prefill_gemm<2>(const LayerArgs&, const int32_t*, const PrefillTables&,
-                                           const PrefillGemm&, bool, hipStream_t);
+                                           const PrefillGemm&, bool, int, hipStream_t);
 }  // namespace mc
