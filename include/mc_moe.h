@@ -191,7 +191,7 @@ typedef struct mc_routing {
  *
  * K (the input width) must be a multiple of 128, at most MC_GPTQ_MAX_K.
  * Workspace: mc_gptq_workspace(R, K) bytes (about 2.25 K^2 doubles for the
- * factor, R K (8 + 1) + 1024 R bytes for the quantizer), 8-byte aligned.
+ * factor, R K (8 + 1) bytes for the quantizer), 8-byte aligned.
  * Errors: MC_EINVAL (shape, NULL or misaligned pointer, damp < 0 or not
  * finite), MC_ENOSPACE (workspace or layer buffers), MC_EHIP. */
 #define MC_GPTQ_MAX_K 32768

@@ -191,6 +191,67 @@ __device__ __forceinline__ int nearest_code(float w, double s, double z, int L) 
   return below;
 }
 
+// The nearest-level decision of nearest_code as fp32
+// comparisons: code = number of j in [0, L) with w > t_j.  With the exact
+// midpoint M_j = s (j + 1/2 - z), the code is the number of even j with
+// w > M_j plus the number of odd j with w >= M_j (a tie goes to the even
+// level), and for an fp32 w either condition is w > t for one fp32 t: the
+// largest value that does not satisfy it.
+__device__ __forceinline__ float fp32_below(float f) {
+  const uint32_t u = __float_as_uint(f);
+  return __uint_as_float((u & 0x7fffffffu) == 0 ? 0x80000001u : (u & 0x80000000u) ? u + 1u : u - 1u);
+}
+
+template <int B>
+__device__ __forceinline__ void code_thresholds(float (&t)[(1 << B) - 1], uint32_t szw) {
+  const double s = (double)half_bits_to_float(szw & 0xffffu);
+  const double z = (double)half_bits_to_float(szw >> 16);
+#pragma unroll
+  for (int j = 0; j < (1 << B) - 1; ++j) {
+    const double m = s * (((double)j + 0.5) - z);     // exact (see nearest_code)
+    const float f = (float)m;
+    const bool step = (j & 1) ? (double)f >= m : (double)f > m;
+    t[j] = step ? fp32_below(f) : f;
+  }
+}
+
+// The thresholds do not decrease, so the count of those below w is found by
+// bisection; threshold_level also picks lev[code].
+template <int B>
+__device__ __forceinline__ uint32_t threshold_code(float w, const float (&t)[(1 << B) - 1]) {
+  if constexpr (B == 1) {
+    return w > t[0] ? 1u : 0u;
+  } else if constexpr (B == 2) {
+    const bool c1 = w > t[1];
+    const bool c0 = w > (c1 ? t[2] : t[0]);
+    return (c1 ? 2u : 0u) + (c0 ? 1u : 0u);
+  } else {
+    const bool c2 = w > t[3];
+    const bool c1 = w > (c2 ? t[5] : t[1]);
+    const float lo = c2 ? t[4] : t[0], hi = c2 ? t[6] : t[2];
+    const bool c0 = w > (c1 ? hi : lo);
+    return (c2 ? 4u : 0u) + (c1 ? 2u : 0u) + (c0 ? 1u : 0u);
+  }
+}
+
+template <int B>
+__device__ __forceinline__ uint32_t threshold_level(float w, const float (&t)[(1 << B) - 1],
+                                                    const double (&lev)[1 << B], double& out) {
+  const uint32_t code = threshold_code<B>(w, t);
+  if constexpr (B == 1) {
+    out = (code & 1u) ? lev[1] : lev[0];
+  } else if constexpr (B == 2) {
+    const double lo = (code & 2u) ? lev[2] : lev[0], hi = (code & 2u) ? lev[3] : lev[1];
+    out = (code & 1u) ? hi : lo;
+  } else {
+    const double a = (code & 4u) ? lev[4] : lev[0], b = (code & 4u) ? lev[5] : lev[1];
+    const double c = (code & 4u) ? lev[6] : lev[2], d = (code & 4u) ? lev[7] : lev[3];
+    const double lo = (code & 2u) ? c : a, hi = (code & 2u) ? d : b;
+    out = (code & 1u) ? hi : lo;
+  }
+  return code;
+}
+
 // Places one code into a lane's b packed words: code pair i (0..15) of the
 // lane's 32 codes, half h (0: first, 1: second of the pair).
 __device__ __forceinline__ void place_code(uint32_t (&w)[3], uint32_t code, int i, int h, int b) {

@@ -24,30 +24,6 @@ namespace mc {
 // scale/zero words and one for the codes, with every midpoint compared in fp64,
 // took 4.94 ms.
 
-// The nearest-level decision of nearest_code (mc_device.hpp) as fp32
-// comparisons: code = number of j in [0, L) with w > t_j.  With the exact
-// midpoint M_j = s (j + 1/2 - z), the code is the number of even j with
-// w > M_j plus the number of odd j with w >= M_j (a tie goes to the even
-// level), and for an fp32 w either condition is w > t for one fp32 t: the
-// largest value that does not satisfy it.
-__device__ __forceinline__ float fp32_below(float f) {
-  const uint32_t u = __float_as_uint(f);
-  return __uint_as_float((u & 0x7fffffffu) == 0 ? 0x80000001u : (u & 0x80000000u) ? u + 1u : u - 1u);
-}
-
-template <int B>
-__device__ __forceinline__ void code_thresholds(float (&t)[(1 << B) - 1], uint32_t szw) {
-  const double s = (double)half_bits_to_float(szw & 0xffffu);
-  const double z = (double)half_bits_to_float(szw >> 16);
-#pragma unroll
-  for (int j = 0; j < (1 << B) - 1; ++j) {
-    const double m = s * (((double)j + 0.5) - z);     // exact (see nearest_code)
-    const float f = (float)m;
-    const bool step = (j & 1) ? (double)f >= m : (double)f > m;
-    t[j] = step ? fp32_below(f) : f;
-  }
-}
-
 // The minimum and maximum over the four lanes of a row (l % 16 equal).
 __device__ __forceinline__ void row_min_max(float& mn, float& mx) {
 #pragma unroll
@@ -86,10 +62,7 @@ __device__ __forceinline__ void pack_tile(const float4 (&v)[8], bool sign, int l
       for (int j = 0; j < 8; ++j) {
         const float4& q = v[2 * u + (j >> 2)];
         const float x = (j & 3) == 0 ? q.x : (j & 3) == 1 ? q.y : (j & 3) == 2 ? q.z : q.w;
-        uint32_t code = 0;
-#pragma unroll
-        for (int i = 0; i < (1 << B) - 1; ++i) code += x > t[i] ? 1u : 0u;
-        place_code(w, code, 4 * u + (j >> 1), j & 1, B);
+        place_code(w, threshold_code<B>(x, t), 4 * u + (j >> 1), j & 1, B);
       }
   }
 #pragma unroll
