@@ -145,20 +145,29 @@ __global__ void __launch_bounds__(kGatherThreads) prefill_prep_kernel(const uint
 
 static size_t round256(size_t b) { return ((b + 255) / 256) * 256; }
 
-// Fragment rows of the m-tiles, from the pairs an expert sees on average.
-// Measured (us a layer call, m-tiles of 1 / 2 / 4 fragment rows): Mixtral
-// layer (G = 128) at 64 tokens 151 / 160 / 237, 128: 194 / 187 / 267, 333:
-// 355 / 305 / 409, 1200: - / 834 / 890; with G = 64 at 96: 192 / 205 / -, 1024:
-// - / 884 / 921, 4096: - / 3110 / 2930; OLMoE layer (G = 64) at 512 tokens: 120
-// / 125 / 163, 2048: 321 / 316 / 358.  Smaller m-tiles unpack (and read) the
-// weights more often but keep more workgroups on a CU.  From 512 pairs an
-// expert on, the 128-token ones: in a short run the 64-token ones are faster
-// there too (Mixtral, 4096 tokens: 2468 against 2573 us), but under sustained
-// load, where the card's power sets the clock, the extra unpacking costs more
-// than it hides (2889 against 2867).
-static int prefill_tiles(int T, int E, int k) {
+// Fragment rows of the m-tiles.  Larger m-tiles unpack (and read) the weights
+// less often, smaller ones keep more workgroups on a CU and leave less padding
+// and a shorter last round, so the choice follows the pairs an expert sees and
+// the gate/up workgroups that 64-token m-tiles would give.  Measured (us a layer
+// call, m-tiles of 1 / 2 / 4 fragment rows):
+//   Mixtral layer (G = 128): 64 tokens 151 / 160 / 237, 128: 190 / 187 / 267,
+//     200: 251 / 233 / 289, 333: 355 / 305 / 409, 1200: - / 834 / 890; G = 64,
+//     1024 tokens: - / 884 / 921, 4096: - / 3110 / 2930
+//   OLMoE layer (G = 64): 512 tokens 120 / 125 / 163, 1024: 189 / 187 / 225,
+//     2048: 321 / 316 / 358
+//   60 experts of 2432 x 2944: 256 tokens 141 / 178 / -, 700: 183 / 202 / 272
+//   tiny layer (256 x 512): 400 tokens 28 / 31 / 46, 2401: 39 / 42 / 53
+//   8 experts of 256 x 9216: 300 tokens 55 / 61 / 102, 800: 84 / 81 / 128,
+//     4096: 308 / 266 / 306
+// The 128-token ones pay off for long reductions and grids of many rounds only:
+// in a short run the 64-token ones are faster there too (Mixtral, 4096 tokens:
+// 2468 against 2573 us), but under sustained load, where the card's power sets
+// the clock, the extra unpacking costs more than it hides (2889 against 2867).
+static int prefill_tiles(int T, int E, int k, int d, int ffn) {
   const double per = (double)T * k / E;
-  return per <= 40 ? 1 : per < 512 ? 2 : 4;
+  const double wgs2 = E * (per / 64 + 0.5) * ffn / 128;     // gate/up workgroups of 64-token m-tiles
+  if (per <= 36 || wgs2 < 1000) return 1;
+  return per >= 512 && wgs2 >= 7000 && d >= 2048 && ffn >= 2048 ? 4 : 2;
 }
 
 // Weight rows of a workgroup (ffn rows of gate/up, d rows of down).
@@ -177,7 +186,7 @@ PrefillLayout prefill_layout(int T, int E, int k, int d, int ffn, int G) {
   PrefillLayout pl;
   const size_t P = (size_t)T * k;
   pl.f_max = (int)((P + (size_t)(kPfFragRows - 1) * E) / kPfFragRows);
-  pl.tiles = prefill_tiles(T, E, k);
+  pl.tiles = prefill_tiles(T, E, k, d, ffn);
   const size_t mtok = (size_t)pl.tiles * kPfFragRows;
   pl.mt_max = (int)((P + (mtok - 1) * E) / mtok);
   // Split the down GEMM's reduction so that its workgroups fill the CUs in
