@@ -23,10 +23,11 @@
 //
 // Otherwise (fewer experts: an MFMA tile would be half empty at 8; or a
 // small batch, where a few tiles leave the GPU idle) one workgroup
-// of 256 threads computes NT tokens x 8 experts with fp64 fmas: each thread
-// takes 16-byte pieces of the d axis, strided by 256 pieces, keeps NT * 8 fp64
-// accumulators, and the partial sums are reduced through LDS and a short
-// shuffle tree in a fixed order.
+// of 256 threads computes NT tokens x NE experts with fp64 fmas: each thread
+// takes 16-byte pieces of the d axis, strided by 256 pieces, and keeps NT * NE
+// fp64 accumulators; a wave's are summed over lane halves and quarters by
+// swapping two accumulators' halves (v_permlane32/16_swap) and adding, which
+// leaves a quarter of them per lane, the rest through LDS in a fixed order.
 #include "mc_internal.hpp"
 
 namespace mc {
@@ -37,38 +38,55 @@ __device__ __forceinline__ double bf16_lo(uint32_t w) { return (double)__uint_as
 __device__ __forceinline__ double bf16_hi(uint32_t w) { return (double)__uint_as_float(w & 0xffff0000u); }
 
 constexpr int kRtThreads = 256;
-constexpr int kRtExperts = 8;
 
-template <int NT>
+// Sum of a and b over the two halves of the wave (SWAP 32) or of each half
+// (SWAP 16): the first half's lanes hold a's sum, the second's b's.
+template <int SWAP>
+__device__ __forceinline__ double swap_add(double a, double b) {
+  const unsigned long long ab = __double_as_longlong(a), bb = __double_as_longlong(b);
+  uint32_t r[4];
+#pragma unroll
+  for (int h = 0; h < 2; ++h) {
+    const uint32_t x = (uint32_t)(ab >> (32 * h)), y = (uint32_t)(bb >> (32 * h));
+    const auto v = SWAP == 32 ? __builtin_amdgcn_permlane32_swap(x, y, false, false)
+                              : __builtin_amdgcn_permlane16_swap(x, y, false, false);
+    r[h] = v[0];
+    r[2 + h] = v[1];
+  }
+  return __longlong_as_double((long long)(((unsigned long long)r[1] << 32) | r[0])) +
+         __longlong_as_double((long long)(((unsigned long long)r[3] << 32) | r[2]));
+}
+
+template <int NT, int NE>
 __global__ void __launch_bounds__(kRtThreads) router_valu_kernel(const uint16_t* __restrict__ x,
                                                             const uint16_t* __restrict__ w, int T, int d,
                                                             int E, float* __restrict__ logits) {
-  constexpr int NO = NT * kRtExperts;            // outputs of the workgroup
+  constexpr int NO = NT * NE;                    // outputs of the workgroup
+  constexpr int NQ = NO / 4;                     // accumulators left per lane after the swaps
   constexpr int PER = kRtThreads / NO;           // threads that finish one output
-  constexpr int SPAN = kRtThreads / PER;         // partials each of them adds first
-  static_assert(kRtThreads % NO == 0 && (PER & (PER - 1)) == 0, "output split");
-  __shared__ double red[NO][kRtThreads];
+  static_assert(NO % 4 == 0 && NO <= 64 && kRtThreads % NO == 0 && (PER & (PER - 1)) == 0, "output split");
+  __shared__ double red[NQ][4][4 * 16 + 2];      // [accumulator][lane quarter][wave and lane]
 
-  const int tid = threadIdx.x;
+  const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
   const int t0 = blockIdx.x * NT;
-  const int e0 = blockIdx.y * kRtExperts;
+  const int e0 = blockIdx.y * NE;
   const int pieces = d >> 3;
 
-  double acc[NT][kRtExperts];
+  double acc[NT][NE];
 #pragma unroll
   for (int i = 0; i < NT; ++i)
 #pragma unroll
-    for (int j = 0; j < kRtExperts; ++j) acc[i][j] = 0.0;
+    for (int j = 0; j < NE; ++j) acc[i][j] = 0.0;
 
   for (int p = tid; p < pieces; p += kRtThreads) {
-    u32x4 xv[NT], wv[kRtExperts];
+    u32x4 xv[NT], wv[NE];
 #pragma unroll
     for (int i = 0; i < NT; ++i) {
       const int t = t0 + i;
       xv[i] = t < T ? *reinterpret_cast<const u32x4*>(x + (size_t)t * d + 8 * p) : u32x4{0u, 0u, 0u, 0u};
     }
 #pragma unroll
-    for (int j = 0; j < kRtExperts; ++j) {
+    for (int j = 0; j < NE; ++j) {
       const int e = e0 + j;
       wv[j] = e < E ? *reinterpret_cast<const u32x4*>(w + (size_t)e * d + 8 * p) : u32x4{0u, 0u, 0u, 0u};
     }
@@ -81,7 +99,7 @@ __global__ void __launch_bounds__(kRtThreads) router_valu_kernel(const uint16_t*
         xh[i] = bf16_hi(xv[i][c]);
       }
 #pragma unroll
-      for (int j = 0; j < kRtExperts; ++j) {
+      for (int j = 0; j < NE; ++j) {
         const double wl = bf16_lo(wv[j][c]), wh = bf16_hi(wv[j][c]);
 #pragma unroll
         for (int i = 0; i < NT; ++i) acc[i][j] = __fma_rn(xh[i], wh, __fma_rn(xl[i], wl, acc[i][j]));
@@ -89,18 +107,29 @@ __global__ void __launch_bounds__(kRtThreads) router_valu_kernel(const uint16_t*
     }
   }
 
+  // output o = i * NE + j: after the two swaps, accumulator q of lane quarter
+  // h (lanes 16 h .. 16 h + 15) holds output 4 q + 2 (h % 2) + h / 2
 #pragma unroll
-  for (int i = 0; i < NT; ++i)
+  for (int q = 0; q < NQ; ++q) {
+    double s[2];
 #pragma unroll
-    for (int j = 0; j < kRtExperts; ++j) red[i * kRtExperts + j][tid] = acc[i][j];
+    for (int b = 0; b < 2; ++b) {
+      const int o = 4 * q + 2 * b;
+      s[b] = swap_add<32>(acc[o / NE][o % NE], acc[(o + 1) / NE][(o + 1) % NE]);
+    }
+    red[q][lane >> 4][16 * wave + (lane & 15)] = swap_add<16>(s[0], s[1]);
+  }
   __syncthreads();
 
+  // PER threads add an output's 64 partials
   const int o = tid / PER, part = tid % PER;
+  const int h = ((o >> 1) & 1) + 2 * (o & 1);
   double s = 0.0;
-  for (int q = 0; q < SPAN; ++q) s += red[o][part * SPAN + q];
+#pragma unroll
+  for (int q = 0; q < 64 / PER; ++q) s += red[o >> 2][h][part * (64 / PER) + q];
 #pragma unroll
   for (int m = PER >> 1; m > 0; m >>= 1) s += __shfl_xor(s, m, PER);
-  const int t = t0 + o / kRtExperts, e = e0 + o % kRtExperts;
+  const int t = t0 + o / NE, e = e0 + o % NE;
   if (part == 0 && t < T && e < E) logits[(size_t)t * E + e] = (float)s;
 }
 
@@ -161,6 +190,31 @@ __global__ void __launch_bounds__(64 * WAVES) router_mfma_kernel(const uint16_t*
   }
 }
 
+// Tokens per workgroup: as many as keep the grid at 256 to 512 workgroups
+// (measured at d = 4096, 8 experts, NT = 1 / 2 / 4 / 8: 2048 tokens 11.7 / 9.0 /
+// 8.6 / 9.2 us, 4096: 21.2 / 16.4 / 13.7 / 12.5, the launch itself about 8; with
+// the 256 partials of every output in LDS and four tokens a workgroup, 4096
+// took 17.4).
+static void launch_router_valu(const uint16_t* x, const uint16_t* w, int T, int d, int E, float* logits,
+                               hipStream_t stream) {
+  const int nt = T <= 512 ? 1 : T <= 1024 ? 2 : T <= 2048 ? 4 : 8;
+#define MC_ROUTER(NT, NE)                                                                                  \
+  hipLaunchKernelGGL((router_valu_kernel<NT, NE>), dim3((T + NT - 1) / NT, (E + NE - 1) / NE), dim3(kRtThreads), 0, \
+                     stream, x, w, T, d, E, logits)
+  if (E <= 4) {
+    if (nt == 1) MC_ROUTER(1, 4);
+    else if (nt == 2) MC_ROUTER(2, 4);
+    else if (nt == 4) MC_ROUTER(4, 4);
+    else MC_ROUTER(8, 4);
+  } else {
+    if (nt == 1) MC_ROUTER(1, 8);
+    else if (nt == 2) MC_ROUTER(2, 8);
+    else if (nt == 4) MC_ROUTER(4, 8);
+    else MC_ROUTER(8, 8);
+  }
+#undef MC_ROUTER
+}
+
 hipError_t launch_router(const uint16_t* x, const uint16_t* w, int T, int d, int E, float* logits,
                          hipStream_t stream) {
   timing_begin(stream, kSiteRouter);
@@ -168,13 +222,7 @@ hipError_t launch_router(const uint16_t* x, const uint16_t* w, int T, int d, int
     hipLaunchKernelGGL(router_mfma_kernel<4>, dim3((T + 15) / 16, (E + 15) / 16), dim3(256), 0, stream, x, w, T,
                        d, E, logits);
   } else {
-    const int eb = (E + kRtExperts - 1) / kRtExperts;
-    if (T <= 256) {
-      hipLaunchKernelGGL(router_valu_kernel<1>, dim3(T, eb), dim3(kRtThreads), 0, stream, x, w, T, d, E, logits);
-    } else {
-      hipLaunchKernelGGL(router_valu_kernel<4>, dim3((T + 3) / 4, eb), dim3(kRtThreads), 0, stream, x, w, T, d, E,
-                         logits);
-    }
+    launch_router_valu(x, w, T, d, E, logits, stream);
   }
   timing_end(stream, kSiteRouter);
   return hipGetLastError();
