@@ -298,10 +298,16 @@ static hipError_t launch_combine(const float* partial, size_t part_stride, int n
 
 hipError_t launch_expert_partials(const uint16_t* x, const LayerArgs& L, const mc_routing& r, void* ws,
                                   float** partial_out, size_t* part_stride_out, int* nsplit_out,
-                                  hipStream_t stream) {
+                                  hipStream_t stream, const RouteArgs* route) {
   const int T = r.T, k = r.k;
-  if (!use_decode(T, r.E, k, L.d, L.ffn))
-    return launch_prefill(x, L, r, ws, partial_out, part_stride_out, nsplit_out, stream);
+  const bool decode = use_decode(T, r.E, k, L.d, L.ffn);
+  if (route && !decode && prefill_routes(T, r.E))
+    return launch_prefill(x, L, r, ws, partial_out, part_stride_out, nsplit_out, stream, route);
+  if (route) {
+    const hipError_t err = launch_route(route->logits, route->important, route->delta32, route->tau, r, stream);
+    if (err != hipSuccess) return err;
+  }
+  if (!decode) return launch_prefill(x, L, r, ws, partial_out, part_stride_out, nsplit_out, stream);
   const size_t P = (size_t)T * k;
   DecodeArgs a;
   a.x = x;
@@ -361,14 +367,10 @@ hipError_t launch_expert_partials(const uint16_t* x, const LayerArgs& L, const m
 hipError_t launch_forward(const uint16_t* x, const LayerArgs& L, const mc_routing& r, uint16_t* y,
                           void* ws, const uint16_t* residual, hipStream_t stream, const RouteArgs* route,
                           uint16_t* xn_next) {
-  if (route) {
-    const hipError_t err = launch_route(route->logits, route->important, route->delta32, route->tau, r, stream);
-    if (err != hipSuccess) return err;
-  }
   float* partial = nullptr;
   size_t part_stride = 0;
   int nsplit = 1;
-  const hipError_t err = launch_expert_partials(x, L, r, ws, &partial, &part_stride, &nsplit, stream);
+  const hipError_t err = launch_expert_partials(x, L, r, ws, &partial, &part_stride, &nsplit, stream, route);
   if (err != hipSuccess) return err;
   return launch_combine(partial, part_stride, nsplit, r, L.d, residual, y, xn_next, stream);
 }

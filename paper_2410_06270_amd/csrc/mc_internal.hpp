@@ -36,6 +36,7 @@ struct RouteBufs {
   float* pair_w;
   int32_t *pair_pos, *n_pruned;
 };
+RouteBufs route_bufs(const mc_routing& r);
 constexpr int kRouteBatch = 8;          // batches routed by one launch_route_batch
 struct RouteBatch {
   RouteBufs r[kRouteBatch];
@@ -63,8 +64,6 @@ struct PrefillLayout {
 };
 PrefillLayout prefill_layout(int T, int E, int k, int d, int ffn, int G);
 size_t prefill_workspace_bytes(int T, int E, int k, int d, int ffn);
-hipError_t launch_prefill(const uint16_t* x, const LayerArgs& L, const mc_routing& r, void* ws,
-                          float** partial, size_t* part_stride, int* nsplit, hipStream_t stream);
 // Routing inputs of a forward call that routes its batch first (the outputs
 // go to the mc_routing buffers as mc_route_and_prune writes them).
 struct RouteArgs {
@@ -73,11 +72,19 @@ struct RouteArgs {
   float delta32;             // fp32 logit-gap threshold (k = 2)
   double tau;                // normalised-weight threshold (k > 2)
 };
+// route (may be null): route the batch in the preparation launch (batches that
+// prefill_routes takes).
+bool prefill_routes(int T, int E);
+hipError_t launch_prefill(const uint16_t* x, const LayerArgs& L, const mc_routing& r, void* ws,
+                          float** partial, size_t* part_stride, int* nsplit, hipStream_t stream,
+                          const RouteArgs* route = nullptr);
 // The expert outputs of every kept pair, unweighted and split over the
 // reduction: partial[s][pos][0..d) for s < nsplit, pos the pair's CSR
 // position (the forward's workspace holds them; launch_forward combines them).
+// route (may be null): route the batch first.
 hipError_t launch_expert_partials(const uint16_t* x, const LayerArgs& L, const mc_routing& r, void* ws,
-                                  float** partial, size_t* part_stride, int* nsplit, hipStream_t stream);
+                                  float** partial, size_t* part_stride, int* nsplit, hipStream_t stream,
+                                  const RouteArgs* route = nullptr);
 // The reconstruction error of Sec. 3.2.2 (pmq.hip): the dense fp32 expert
 // outputs of every kept pair (h [P][ffn], y [P][d], fp32 weights [E][N][K]),
 // and eps[e][b-1] from the packed forward's per-pair partials against them.

@@ -3,6 +3,7 @@
 // and their launcher.  The GEMM kernels are in prefill.hpp, one file per
 // group size.
 #include "prefill.hpp"
+#include "route_device.hpp"
 #include <algorithm>
 
 namespace mc {
@@ -143,6 +144,90 @@ __global__ void __launch_bounds__(kGatherThreads) prefill_prep_kernel(const uint
   }
 }
 
+// Routing and preparation in one launch, for batches that one workgroup
+// routes: every workgroup (fragment row f, block of kGatherCols columns) routes
+// the whole batch in its LDS (a few us that a launch of its own would take too,
+// and its results are at hand: no second launch, no tables to read back), takes
+// f's rows from the experts' token masks and gathers its block as
+// prefill_prep_kernel does; the first workgroup publishes the routing and the
+// GEMMs' tables.  Tiny layer (4 experts), 64 tokens: 4.8 + 5.0 us in two
+// launches, 6.9 in one, 24.4 -> 21.4 a call; Mixtral layer (8), 64 tokens: 5.6 +
+// 6.3 and 7.6.  With many experts the selection is long and the fragment rows
+// many, two workgroups a CU: OLMoE layer (64), 16 tokens: 7.8 + 5.5 us in two
+// launches, 13.8 in one, so those keep them.
+template <int GP>
+__global__ void __launch_bounds__(64 * kRouteWaves) route_prep_kernel(
+    const float* __restrict__ logits, const uint8_t* __restrict__ important, int T, int E, int k, float delta32,
+    double tau, RouteBufs o, const uint16_t* __restrict__ x, int d, PrefillTables tb, uint16_t* __restrict__ xt,
+    float* __restrict__ xsum) {
+  __shared__ RouteSmallLds s;
+  static_assert(kPfFragRows * kGatherStride * 2 <= (int)sizeof(s.scratch), "the gather tile reuses the scratch");
+  static_assert(kPfFragRows == 2 * kRouteWaves, "two rows a wave");
+  const int lane = threadIdx.x & 63, wave = wave_id();
+  const int f = blockIdx.x;
+  const bool first = blockIdx.x == 0 && blockIdx.y == 0;
+  route_small_batch(s, logits, important, T, E, k, delta32, tau, o, first);
+  __syncthreads();
+  // tables: lane e of every wave holds expert e (prefill_routes: E <= 16)
+  const int nf = lane < E ? (s.cnt[lane] + kPfFragRows - 1) / kPfFragRows : 0;
+  const int nm = (nf + tb.tiles - 1) / tb.tiles;
+  int sf = nf, sm = nm;
+#pragma unroll
+  for (int off = 1; off < 64; off <<= 1) {
+    const int a = __shfl_up(sf, off), b = __shfl_up(sm, off);
+    if (lane >= off) {
+      sf += a;
+      sm += b;
+    }
+  }
+  const int tf = __builtin_amdgcn_readlane(sf, 63), fb = sf - nf, mb = sm - nm;
+  if (first && wave == 0) {
+    if (lane < E) {
+      tb.ftile_base[lane] = fb;
+      for (int i = 0; i < nm; ++i) {
+        tb.mt_e[mb + i] = lane;
+        tb.mt_j[mb + i] = i;
+      }
+    }
+    if (lane == 63) {
+      tb.ftile_base[E] = sf;
+      *tb.mt_count = sm;
+    }
+  }
+  if (f >= tf) return;   // workgroup-uniform
+  const int e = __builtin_ctzll(__ballot(fb <= f && f < fb + nf));   // exactly one expert holds f
+  const int r0 = kPfFragRows * (f - __builtin_amdgcn_readlane(fb, e));
+  // lane t: token t's place in e's list
+  const unsigned long long mask = s.bal[e];
+  const bool on_list = (mask >> lane) & 1ull;
+  const int place = __popcll(mask & ((1ull << lane) - 1ull));
+  const int c0 = blockIdx.y * kGatherCols;
+  const int w = (d - c0) < kGatherCols ? (d - c0) : kGatherCols;   // a multiple of 128
+  const bool on = 8 * lane < w;
+  const int ng = d / (8 * GP);
+  uint16_t* tile = reinterpret_cast<uint16_t*>(&s.scratch[0][0]);   // the selections are done
+#pragma unroll
+  for (int j = 0; j < 2; ++j) {
+    const int m = 2 * wave + j;
+    const unsigned long long who = __ballot(on_list && place == r0 + m);
+    u32x4 v = u32x4{0u, 0u, 0u, 0u};
+    if (on && who) v = *reinterpret_cast<const u32x4*>(x + (size_t)__builtin_ctzll(who) * d + c0 + 8 * lane);
+    if (on) *reinterpret_cast<u32x4*>(tile + m * kGatherStride + 8 * lane) = v;
+    const float sum = lane_group_sum<GP>(sum8<false>(v));
+    if (on && lane % GP == 0) xsum[((size_t)f * ng + (c0 + 8 * lane) / (8 * GP)) * 32 + m] = sum;
+  }
+  __syncthreads();
+  unsigned char* out = reinterpret_cast<unsigned char*>(xt) + frag_offset(f, 0, 0, d);
+  const int pieces = (w / 16) * 64;
+  for (int p = threadIdx.x; p < pieces; p += 64 * kRouteWaves) {
+    const int fi = p >> 6, mm = p & 63;
+    *reinterpret_cast<u32x4*>(out + ((size_t)(c0 / 16 + fi) * 64 + mm) * 16) =
+        *reinterpret_cast<const u32x4*>(tile + (mm & 31) * kGatherStride + 16 * fi + 8 * (mm >> 5));
+  }
+}
+
+bool prefill_routes(int T, int E) { return E <= 16 && route_fused_fits(T, E); }
+
 static size_t round256(size_t b) { return ((b + 255) / 256) * 256; }
 
 // Fragment rows of the m-tiles.  Larger m-tiles unpack (and read) the weights
@@ -232,7 +317,8 @@ size_t prefill_workspace_bytes(int T, int E, int k, int d, int ffn) {
 }
 
 hipError_t launch_prefill(const uint16_t* x, const LayerArgs& L, const mc_routing& r, void* ws,
-                          float** partial, size_t* part_stride, int* nsplit, hipStream_t stream) {
+                          float** partial, size_t* part_stride, int* nsplit, hipStream_t stream,
+                          const RouteArgs* route) {
   const PrefillLayout pl = prefill_layout(r.T, r.E, r.k, L.d, L.ffn, L.G);
   char* base = static_cast<char*>(ws);
   PrefillTables tb;
@@ -255,17 +341,27 @@ hipError_t launch_prefill(const uint16_t* x, const LayerArgs& L, const mc_routin
   *nsplit = pl.nsplit;
 
   const dim3 pgrid(pl.f_max, (L.d + kGatherCols - 1) / kGatherCols);
-  timing_begin(stream, kSitePrefillPrep);
-  if (L.G == 128)
-    hipLaunchKernelGGL(prefill_prep_kernel<16>, pgrid, dim3(kGatherThreads), 0, stream, x, L.d, r.E,
-                       r.counts, r.offsets, r.pair_token, tb, xt, xsum);
-  else if (L.G == 64)
-    hipLaunchKernelGGL(prefill_prep_kernel<8>, pgrid, dim3(kGatherThreads), 0, stream, x, L.d, r.E,
-                       r.counts, r.offsets, r.pair_token, tb, xt, xsum);
-  else
-    hipLaunchKernelGGL(prefill_prep_kernel<4>, pgrid, dim3(kGatherThreads), 0, stream, x, L.d, r.E,
-                       r.counts, r.offsets, r.pair_token, tb, xt, xsum);
-  timing_end(stream, kSitePrefillPrep);
+  if (route) {
+    timing_begin(stream, kSiteRouteFused);
+#define MC_ROUTE_PREP(GP)                                                                                     \
+  hipLaunchKernelGGL(route_prep_kernel<GP>, pgrid, dim3(64 * kRouteWaves), 0, stream, route->logits,          \
+                     route->important, r.T, r.E, r.k, route->delta32, route->tau, route_bufs(r), x, L.d, tb, xt, xsum)
+    if (L.G == 128) MC_ROUTE_PREP(16);
+    else if (L.G == 64) MC_ROUTE_PREP(8);
+    else MC_ROUTE_PREP(4);
+#undef MC_ROUTE_PREP
+    timing_end(stream, kSiteRouteFused);
+  } else {
+    timing_begin(stream, kSitePrefillPrep);
+#define MC_PREP(GP)                                                                                           \
+  hipLaunchKernelGGL(prefill_prep_kernel<GP>, pgrid, dim3(kGatherThreads), 0, stream, x, L.d, r.E, r.counts,  \
+                     r.offsets, r.pair_token, tb, xt, xsum)
+    if (L.G == 128) MC_PREP(16);
+    else if (L.G == 64) MC_PREP(8);
+    else MC_PREP(4);
+#undef MC_PREP
+    timing_end(stream, kSitePrefillPrep);
+  }
   hipError_t err = hipGetLastError();
   if (err != hipSuccess) return err;
 

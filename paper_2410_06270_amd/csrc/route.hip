@@ -22,7 +22,7 @@
 
 namespace mc {
 
-constexpr int kCsrThreads = 1024;
+constexpr int kCsrThreads = 64 * kRouteWaves;
 constexpr int kListBlocks = 64;     // at most this many token blocks scatter the lists
 constexpr int kListMaxBlockT = 1024;
 static_assert(kListBlocks * kListMaxBlockT >= MC_MAX_TOKENS, "list blocks cover every token");
@@ -117,52 +117,11 @@ __global__ void __launch_bounds__(kCsrThreads) route_scatter_kernel(
               pair_w, pair_pos);
 }
 
-// Small batches run in one launch: at most kRouteFusedMaxT tokens (a lane per
-// token in the lists) that one round of the workgroup's 16 waves selects
-// (64/S tokens a wave; measured: 64 experts, 16 tokens: 8.6 us against 11.0
-// in two launches).  With more than 64 experts a lane ranks several keys and
-// a selection is slower: there T * E <= 512 (as measured at 64 experts before
-// the ranks were batched: 32 tokens took 20 us against 11.5 in two launches).
-// Larger batches spread the selections over many CUs.
-__host__ __device__ constexpr bool route_fused_fits(int T, int E) {
-  return T <= kRouteFusedMaxT && (E <= 64 ? T <= (kCsrThreads / 64) * (64 / sel_segment(E)) : T * E <= 512);
-}
-
-// The small-batch routing of one batch (a workgroup): the waves select the
-// tokens side by side (the selections kept in LDS), then wave 0 builds the
-// lists (small_batch_lists).
-__device__ __forceinline__ void route_fused_body(const float* __restrict__ logits,
-                                                 const uint8_t* __restrict__ important, int T, int E, int k,
-                                                 float delta32, double tau, const RouteBufs& o) {
-  static_assert(kRouteFusedMaxT <= 64, "one lane per token");
-  __shared__ uint16_t ent[kRouteFusedMaxT * MC_MAX_TOPK];
-  __shared__ float wsel[kRouteFusedMaxT * MC_MAX_TOPK];
-  __shared__ int cnt[MC_MAX_EXPERTS];
-  __shared__ int base[MC_MAX_EXPERTS + 1];
-  __shared__ unsigned long long bal[MC_MAX_EXPERTS];
-  __shared__ __attribute__((aligned(16))) unsigned char scratch[kCsrThreads / 64][kSelScratchBytes];
-  const int wave = wave_id(), nwaves = blockDim.x >> 6;
-  const SelScratch sc = sel_scratch(scratch[wave]);
-  const int S = sel_segment(E), ns = 64 / S;
-  // a wave selects ns tokens at once; route_fused_fits makes one round of
-  // the 16 waves enough
-  for (int t0 = wave * ns; t0 < T; t0 += nwaves * ns) {
-    const int t = t0 + (threadIdx.x & 63) / S;
-    const SelInput in = sel_load(logits, important, t, T, E, S);
-    select_token(in, t, T, E, S, k, delta32, tau, o.topk_idx, o.topk_w, o.kept, o.pair_pos, true, ent, wsel,
-                 sc);
-  }
-  __syncthreads();
-  if (wave != 0) return;
-  const RouteLds s{ent, wsel, cnt, base, bal};
-  small_batch_lists(T, E, k, s, true, o.counts, o.offsets, o.pair_token, o.pair_rank, o.pair_w, o.pair_pos,
-                    o.n_pruned);
-}
-
 __global__ void __launch_bounds__(kCsrThreads) route_fused_kernel(
     const float* __restrict__ logits, const uint8_t* __restrict__ important, int T, int E, int k,
     float delta32, double tau, RouteBufs o) {
-  route_fused_body(logits, important, T, E, k, delta32, tau, o);
+  __shared__ RouteSmallLds s;
+  route_small_batch(s, logits, important, T, E, k, delta32, tau, o, true);
 }
 
 // Several batches of the same shape at once, one workgroup each: batch b's
@@ -172,11 +131,12 @@ __global__ void __launch_bounds__(kCsrThreads) route_fused_batch_kernel(
     const float* __restrict__ logits, const uint8_t* __restrict__ important, int T, int E, int k,
     float delta32, double tau, RouteBatch o) {
   const size_t b = blockIdx.x;
-  route_fused_body(logits + b * T * E, important ? important + b * T : nullptr, T, E, k, delta32, tau,
-                   o.r[b]);
+  __shared__ RouteSmallLds s;
+  route_small_batch(s, logits + b * T * E, important ? important + b * T : nullptr, T, E, k, delta32, tau, o.r[b],
+                    true);
 }
 
-static RouteBufs route_bufs(const mc_routing& r) {
+RouteBufs route_bufs(const mc_routing& r) {
   return RouteBufs{r.topk_idx, r.topk_w, r.kept, r.counts, r.offsets, r.pair_token, r.pair_rank, r.pair_w,
                    r.pair_pos, r.n_pruned};
 }

@@ -267,4 +267,52 @@ static __device__ void small_batch_lists(int T, int E, int k, const RouteLds& s,
   }
 }
 
+constexpr int kRouteWaves = 16;     // waves of the workgroup that routes a small batch
+
+// Small batches run in one workgroup: at most kRouteFusedMaxT tokens (a lane per
+// token in the lists) that one round of the workgroup's 16 waves selects
+// (64/S tokens a wave; measured: 64 experts, 16 tokens: 8.6 us against 11.0
+// in two launches).  With more than 64 experts a lane ranks several keys and
+// a selection is slower: there T * E <= 512 (as measured at 64 experts before
+// the ranks were batched: 32 tokens took 20 us against 11.5 in two launches).
+// Larger batches spread the selections over many CUs.
+__host__ __device__ constexpr bool route_fused_fits(int T, int E) {
+  return T <= kRouteFusedMaxT && (E <= 64 ? T <= kRouteWaves * (64 / sel_segment(E)) : T * E <= 512);
+}
+
+struct RouteSmallLds {
+  __attribute__((aligned(16))) unsigned char scratch[kRouteWaves][kSelScratchBytes];
+  unsigned long long bal[MC_MAX_EXPERTS];
+  uint16_t ent[kRouteFusedMaxT * MC_MAX_TOPK];
+  float wsel[kRouteFusedMaxT * MC_MAX_TOPK];
+  int cnt[MC_MAX_EXPERTS];
+  int base[MC_MAX_EXPERTS + 1];
+};
+
+// The small-batch routing of one batch by one workgroup of kRouteWaves waves:
+// the waves select the tokens side by side (the selections kept in LDS), then
+// wave 0 builds the lists (small_batch_lists; s.cnt and s.bal are complete at
+// the workgroup's next barrier).  Outputs go to memory with `publish`.
+__device__ __forceinline__ void route_small_batch(RouteSmallLds& s, const float* __restrict__ logits,
+                                         const uint8_t* __restrict__ important, int T, int E, int k, float delta32,
+                                         double tau, const RouteBufs& o, bool publish) {
+  static_assert(kRouteFusedMaxT <= 64, "one lane per token");
+  const int wave = wave_id();
+  const SelScratch sc = sel_scratch(s.scratch[wave]);
+  const int S = sel_segment(E), ns = 64 / S;
+  // a wave selects ns tokens at once; route_fused_fits makes one round of
+  // the 16 waves enough
+  for (int t0 = wave * ns; t0 < T; t0 += kRouteWaves * ns) {
+    const int t = t0 + (threadIdx.x & 63) / S;
+    const SelInput in = sel_load(logits, important, t, T, E, S);
+    select_token(in, t, T, E, S, k, delta32, tau, o.topk_idx, o.topk_w, o.kept, o.pair_pos, publish, s.ent, s.wsel,
+                 sc);
+  }
+  __syncthreads();
+  if (wave != 0) return;
+  const RouteLds r{s.ent, s.wsel, s.cnt, s.base, s.bal};
+  small_batch_lists(T, E, k, r, publish, o.counts, o.offsets, o.pair_token, o.pair_rank, o.pair_w, o.pair_pos,
+                    o.n_pruned);
+}
+
 }  // namespace mc
