@@ -228,7 +228,8 @@ mc_status mc_router_logits(const uint16_t *x_bf16, const uint16_t *w_router_bf16
 mc_status mc_route_and_prune(const float *logits, const uint8_t *important,
                              float threshold, const mc_routing *r, void *stream);
 
-/* Workspace bytes mc_moe_forward needs for T tokens. Errors: MC_EINVAL. */
+/* Workspace bytes mc_moe_forward needs for T tokens; they serve every smaller
+ * batch of the same shape too. Errors: MC_EINVAL. */
 mc_status mc_forward_workspace(int T, int E, int k, int d, int ffn, size_t *bytes);
 
 /* Eq. 1 over the kept pairs: y_t = sum_r w_r * E_{e_r}(x_t) with
@@ -250,7 +251,7 @@ mc_status mc_moe_forward(const uint16_t *x_bf16, const mc_routing *r,
  * contents (the forward writes every workspace byte it reads, nothing needs
  * clearing): calls that overlap on one GPU (other streams, other threads)
  * race and must be serialised by the caller.  Errors: as mc_moe_forward;
- * MC_ENOSPACE when mc_forward_workspace(T, ...) exceeds the array (decode
+ * MC_ENOSPACE when the batch's own workspace exceeds the array (decode
  * batches of up to 64 tokens of the Mixtral-shaped layer fit). */
 #define MC_NOALLOC_SCRATCH_BYTES (32u << 20)
 mc_status mc_moe_forward_noalloc(const uint16_t *x_bf16, const mc_routing *r,

@@ -329,7 +329,7 @@ mc_status mc_forward_workspace(int T, int E, int k, int d, int ffn, size_t* byte
     return fail(MC_EINVAL, "bad shape T=%d E=%d k=%d d=%d ffn=%d", T, E, k, d, ffn);
   if (T > MC_MAX_TOKENS) return fail(MC_EUNSUPPORTED, "T=%d above %d", T, MC_MAX_TOKENS);
   if (!bytes) return fail(MC_EINVAL, "bytes pointer is NULL");
-  *bytes = mc::forward_workspace_bytes(T, E, k, d, ffn);
+  *bytes = mc::forward_workspace_upto(T, E, k, d, ffn);
   return MC_OK;
 }
 
@@ -403,7 +403,9 @@ mc_status mc_pmq_error_workspace(int T, int E, int k, int d, int ffn, int group,
   std::vector<int> three(E, 3);
   s = check_shape(E, d, ffn, three.data(), group);
   if (s != MC_OK) return s;
-  *bytes = pmq_layout(T, E, k, d, ffn, group).total;
+  // as mc_forward_workspace: enough for every smaller batch too
+  *bytes = pmq_layout(T, E, k, d, ffn, group).total - up256(mc::forward_workspace_bytes(T, E, k, d, ffn)) +
+           up256(mc::forward_workspace_upto(T, E, k, d, ffn));
   return MC_OK;
 }
 
@@ -418,8 +420,8 @@ mc_status mc_pmq_expert_error(const float* w_gate, const float* w_up, const floa
   if (s != MC_OK) return s;
   if (!w_gate || !w_up || !w_down || !x_bf16 || !eps_host || !workspace)
     return fail(MC_EINVAL, "weight, x, eps or workspace pointer is NULL");
-  if (ws_bytes < need) return fail(MC_ENOSPACE, "workspace %zu bytes, need %zu", ws_bytes, need);
   const PmqLayout o = pmq_layout(r->T, E, r->k, d, ffn, group);
+  if (ws_bytes < o.total) return fail(MC_ENOSPACE, "workspace %zu bytes, need %zu", ws_bytes, o.total);
   char* ws = static_cast<char*>(workspace);
   float* h = reinterpret_cast<float*>(ws + o.h);
   float* y = reinterpret_cast<float*>(ws + o.y);
@@ -463,7 +465,7 @@ mc_status mc_pmq_expert_error(const float* w_gate, const float* w_up, const floa
 mc_status mc_stack_workspace(int T, int E, int k, int d, int ffn, size_t* bytes) {
   mc_status s = mc_forward_workspace(T, E, k, d, ffn, bytes);
   if (s != MC_OK) return s;
-  *bytes = mc::stack_workspace_bytes(T, E, k, d, ffn);
+  *bytes = mc::stack_workspace_upto(T, E, k, d, ffn);
   return MC_OK;
 }
 

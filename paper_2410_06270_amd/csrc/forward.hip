@@ -2,6 +2,7 @@
 // (decode GEMVs: decode.hpp, prefill GEMMs: prefill.hpp, one file per group
 // size each).
 #include "decode.hpp"
+#include <algorithm>
 
 namespace mc {
 
@@ -232,6 +233,16 @@ size_t forward_workspace_bytes(int T, int E, int k, int d, int ffn) {
   return h + gu + part;
 }
 
+// What the workspace queries answer: enough for T tokens and for every smaller
+// batch (a serving program sizes its workspace once).  The GEMMs' workspace
+// does not grow steadily with T (their m-tiles and splits change), and a batch
+// whose GEMM workspace is too large keeps the GEMVs, whose own is small.
+size_t forward_workspace_upto(int T, int E, int k, int d, int ffn) {
+  size_t most = 0;
+  for (int t = 1; t <= T; ++t) most = std::max(most, forward_workspace_bytes(t, E, k, d, ffn));
+  return most;
+}
+
 size_t routing_set_bytes(int T, int E, int k) {
   const size_t P = (size_t)T * k;
   return 6 * round256(P * 4) + round256(P) + round256((size_t)E * 4) + round256(((size_t)E + 1) * 4) + 256;
@@ -265,6 +276,14 @@ mc_routing routing_set(void* base, int T, int E, int k) {
 size_t stack_workspace_bytes(int T, int E, int k, int d, int ffn) {
   const size_t routes = route_batch_fits(T, E) ? (size_t)kRouteBatch * routing_set_bytes(T, E, k) : 0;
   return round256((size_t)T * d * sizeof(uint16_t)) + routes + forward_workspace_bytes(T, E, k, d, ffn);
+}
+
+size_t stack_workspace_upto(int T, int E, int k, int d, int ffn) {
+  // at least the parts of T beside the largest forward workspace
+  size_t most = stack_workspace_bytes(T, E, k, d, ffn) - forward_workspace_bytes(T, E, k, d, ffn) +
+                forward_workspace_upto(T, E, k, d, ffn);
+  for (int t = 1; t < T; ++t) most = std::max(most, stack_workspace_bytes(t, E, k, d, ffn));
+  return most;
 }
 
 static hipError_t launch_combine(const float* partial, size_t part_stride, int nsplit,

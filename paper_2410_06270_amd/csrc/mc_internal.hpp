@@ -53,7 +53,9 @@ hipError_t launch_route_batch(const float* logits, const uint8_t* important, flo
 // and the set laid out at base.
 size_t routing_set_bytes(int T, int E, int k);
 mc_routing routing_set(void* base, int T, int E, int k);
+// What a call of T tokens needs, and what serves every batch of up to T.
 size_t forward_workspace_bytes(int T, int E, int k, int d, int ffn);
+size_t forward_workspace_upto(int T, int E, int k, int d, int ffn);
 // Workspace of the prefill path (byte offsets): expert tile tables, the
 // fragment-tiled copies of the routed x rows (bf16) and of h (fp16) with their
 // 32-column sums, and the fp32 down partials [nsplit][T*k][d].
@@ -106,6 +108,7 @@ hipError_t launch_rmsnorm(const uint16_t* h, int T, int d, double eps, uint16_t*
 // xn [T][d], the routing sets of kRouteBatch layers when route_batch_fits,
 // and the forward workspace.
 size_t stack_workspace_bytes(int T, int E, int k, int d, int ffn);
+size_t stack_workspace_upto(int T, int E, int k, int d, int ffn);
 // logits [T][E] fp32 = x [T][d] . w [E][d]^T (bf16), fp64 sums rounded once.
 hipError_t launch_router(const uint16_t* x, const uint16_t* w, int T, int d, int E, float* logits,
                          hipStream_t stream);

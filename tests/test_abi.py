@@ -138,6 +138,21 @@ def _round256(b):
     return (b + 255) // 256 * 256
 
 
+@pytest.mark.parametrize("shape", [(64, 1, 2048, 4096), (60, 2, 1024, 4096), (8, 2, 4096, 14336), (4, 2, 256, 512)])
+@pytest.mark.parametrize("query", ["mc_forward_workspace", "mc_stack_workspace", "mc_pmq_error_workspace"])
+def test_workspace_serves_smaller_batches(lib, query, shape):
+    """A workspace of T tokens holds every smaller batch: the queries never
+    fall as T grows, whichever kernels the sizes take."""
+    def ws(T):
+        b = ctypes.c_size_t()
+        args = (T, *shape) + ((64,) if "pmq" in query else ())
+        assert getattr(lib, query)(*args, ctypes.byref(b)) == 0
+        return b.value
+
+    sizes = [ws(T) for T in [*range(1, 130), *range(130, 4097, 61)]]
+    assert sizes == sorted(sizes)
+
+
 def test_stack_workspace(lib):
     """mc_stack_workspace = the normalised input + (batches routed by one
     workgroup: T <= 64 and T <= 16*64/S) the routing buffers of 8 layers +
