@@ -531,11 +531,13 @@ struct QuantGroup {
 
 // a / b correctly rounded, y = 1 / b correctly rounded: two corrections of
 // a y by the exact remainder (Markstein 1990: the first gives a faithful
-// quotient, the second the rounded one).  b finite and not tiny.
+// quotient, the second the rounded one).  b finite and not tiny; the fix-up
+// puts the quotients of infinities, NaN and zeros in place (the corrections
+// would make a NaN of an infinite a).
 __device__ __forceinline__ double quotient(double a, double b, double y) {
   double q = a * y;
   q = __fma_rn(__fma_rn(-q, b, a), y, q);
-  return __fma_rn(__fma_rn(-q, b, a), y, q);
+  return __builtin_amdgcn_div_fixup(__fma_rn(__fma_rn(-q, b, a), y, q), b, a);
 }
 
 // Columns 4 i .. 4 i + 3 of the block; v[t] is column 4 (i + t) + sub, N of them

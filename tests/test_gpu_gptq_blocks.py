@@ -49,6 +49,27 @@ def test_quantize_blocks_bit_exact(R, K, bits, G):
     np.testing.assert_array_equal(got[same], want[same])
 
 
+def test_quantize_infinite_weight():
+    """An infinite weight in the last column: its error, and so the row's loss,
+    is infinite (a division's, not a NaN); the other rows are untouched."""
+    import paper_2410_06270_amd as mc
+    R, K, G = 128, 128, 32
+    W = np.random.default_rng(3).standard_normal((R, K)).astype(np.float32) * np.float32(0.02)
+    W[5, K - 1] = np.inf
+    W[9, K - 1] = -np.inf
+    U, dead = oracle.gptq_factor(oracle.gptq_hessian(synthetic.calibration(1, 2 * K, K, tag=K)))
+    L = mc.PackedLayer(1, K, R, [2], G)
+    ws = torch.empty(mc.gptq_workspace(R, K), dtype=torch.uint8, device="cuda")
+    loss = torch.empty(R, dtype=torch.float64, device="cuda")
+    mc.gptq_quantize(L, 0, 0, to_dev(W), to_dev(U), to_dev(dead), ws, loss=loss)
+    torch.cuda.synchronize()
+    loss = loss.cpu().numpy()
+    assert loss[5] == np.inf
+    rows = [r for r in range(R) if r not in (5, 9)]
+    want = oracle.gptq_quantize_u(W[rows], U, dead, 2, G)[3]
+    np.testing.assert_allclose(loss[rows], want, rtol=1e-12)
+
+
 @pytest.mark.parametrize("K", [128, 384, 640, 896])
 def test_factor_uneven_merges(K):
     import paper_2410_06270_amd as mc
