@@ -103,15 +103,26 @@ __device__ __forceinline__ void imp_add_rows(float (&acc)[8], const u32x4* v, in
 
 // Full tiles with VEC (L a multiple of 8, 16-byte aligned map): per head, the
 // thread's 8 rows as 16-byte loads, all issued before any is used (with 4+
-// waves per SIMD that keeps enough bytes in flight to stream HBM).
+// waves per SIMD that keeps enough bytes in flight to stream HBM).  STREAM:
+// non-temporal loads, for maps of which the memory-side cache (256 MB) cannot
+// hold what their producer wrote (32 heads of 4096 tokens, 537 MB read, the whole
+// call: 111 -> 101 us, 5.7 TB/s); smaller ones may still be found there.
 // di0 = first row - j0.
-template <bool DIAG>
+constexpr double kImpStreamBytes = 384e6;   // one and a half times the cache
+
+template <bool STREAM>
+__device__ __forceinline__ u32x4 imp_load(const uint16_t* p) {
+  if (STREAM) return __builtin_nontemporal_load(reinterpret_cast<const u32x4*>(p));
+  return *reinterpret_cast<const u32x4*>(p);
+}
+
+template <bool DIAG, bool STREAM>
 __device__ __forceinline__ void imp_full_tile(float (&acc)[8], const uint16_t* p, size_t hstride, size_t rstride,
                                               int nh, int di0) {
   for (int h = 0; h < nh; ++h, p += hstride) {
     u32x4 v[8];
 #pragma unroll
-    for (int k = 0; k < 8; ++k) v[k] = *reinterpret_cast<const u32x4*>(p + k * rstride);
+    for (int k = 0; k < 8; ++k) v[k] = imp_load<STREAM>(p + k * rstride);
     imp_add_rows<DIAG>(acc, v, di0);
   }
 }
@@ -127,6 +138,7 @@ __device__ __forceinline__ float imp_abs_sum8(const u32x4& v) {
 // loads (d a multiple of 8, x 16-byte aligned), 8 in flight per lane.
 constexpr int kNormTokens = 16;
 
+template <bool STREAM>
 __device__ void imp_norms(const uint16_t* __restrict__ x, int L, int d, bool xvec, int blk,
                           float* __restrict__ norms) {
   const int lane = threadIdx.x & 63, nw = kImpThreads / 64;
@@ -138,7 +150,7 @@ __device__ void imp_norms(const uint16_t* __restrict__ x, int L, int d, bool xve
       for (; c + 7 * 512 < d; c += 8 * 512) {
         u32x4 v[8];
 #pragma unroll
-        for (int k = 0; k < 8; ++k) v[k] = *reinterpret_cast<const u32x4*>(xr + c + 512 * k);
+        for (int k = 0; k < 8; ++k) v[k] = imp_load<STREAM>(xr + c + 512 * k);
 #pragma unroll
         for (int k = 0; k < 8; ++k) n1 += imp_abs_sum8(v[k]);
       }
@@ -156,7 +168,7 @@ __device__ void imp_norms(const uint16_t* __restrict__ x, int L, int d, bool xve
 // 8cg..8cg+7 of the key tile.  Full tiles take imp_full_tile (the diagonal one
 // masking j > i after the load); ragged tiles and maps without VEC check every
 // element against i >= j and the map's edge.
-template <bool VEC>
+template <bool VEC, bool STREAM>
 __device__ void imp_colsum_tile(const uint16_t* __restrict__ attn, int H, int L, int hpw, int pair, int slice,
                                 float* __restrict__ out) {
   __shared__ float red[16][kImpTile + 4];
@@ -172,9 +184,9 @@ __device__ void imp_colsum_tile(const uint16_t* __restrict__ attn, int H, int L,
     const int i0 = tq * kImpTile + r;
     const uint16_t* p = attn + (size_t)h0 * hstride + (size_t)i0 * L + j0;
     if (tq > tk)
-      imp_full_tile<false>(acc, p, hstride, rstride, h1 - h0, 0);
+      imp_full_tile<false, STREAM>(acc, p, hstride, rstride, h1 - h0, 0);
     else
-      imp_full_tile<true>(acc, p, hstride, rstride, h1 - h0, i0 - j0);
+      imp_full_tile<true, STREAM>(acc, p, hstride, rstride, h1 - h0, i0 - j0);
   } else {
     for (int h = h0; h < h1; ++h) {
       const uint16_t* ah = attn + (size_t)h * hstride;
@@ -205,7 +217,7 @@ __device__ void imp_colsum_tile(const uint16_t* __restrict__ attn, int H, int L,
 // One launch, two kinds of workgroup: the first n_norm blocks compute the l1
 // norms (dispatched first, they overlap the attention stream), the rest one
 // (head slice, tile pair) each, slice-major, writing partial[block][128].
-template <bool VEC>
+template <bool VEC, bool STREAM>
 __global__ void __launch_bounds__(kImpThreads) importance_colsum_kernel(const uint16_t* __restrict__ attn, int H,
                                                                         int L, int hpw, int n_norm,
                                                                         const uint16_t* __restrict__ x, int d,
@@ -213,11 +225,11 @@ __global__ void __launch_bounds__(kImpThreads) importance_colsum_kernel(const ui
                                                                         float* __restrict__ partial) {
   const int b = blockIdx.x;
   if (b < n_norm) {
-    imp_norms(x, L, d, xvec, b, norms);
+    imp_norms<STREAM>(x, L, d, xvec, b, norms);
     return;
   }
   const int t = b - n_norm, pairs = imp_tiles(L) * (imp_tiles(L) + 1) / 2;
-  imp_colsum_tile<VEC>(attn, H, L, hpw, t % pairs, t / pairs, partial + (size_t)t * kImpTile);
+  imp_colsum_tile<VEC, STREAM>(attn, H, L, hpw, t % pairs, t / pairs, partial + (size_t)t * kImpTile);
 }
 
 // One wave per key j (4 per workgroup): the key's partial sums over its query
@@ -355,11 +367,15 @@ hipError_t launch_importance(const uint16_t* attn, int H, int L, const uint16_t*
   const int n_norm = (L + kNormTokens - 1) / kNormTokens;
   const dim3 cgrid(n_norm + imp_pairs(L) * hs);
   timing_begin(stream, kSiteImpColsum);
-  if (vec)
-    hipLaunchKernelGGL((importance_colsum_kernel<true>), cgrid, dim3(kImpThreads), 0, stream, attn, H, L, hpw,
+  const bool stream_map = vec && (double)H * L * (L + 1.0) >= kImpStreamBytes;
+  if (stream_map)
+    hipLaunchKernelGGL((importance_colsum_kernel<true, true>), cgrid, dim3(kImpThreads), 0, stream, attn, H, L, hpw,
+                       n_norm, x, d, xvec, norms, partial);
+  else if (vec)
+    hipLaunchKernelGGL((importance_colsum_kernel<true, false>), cgrid, dim3(kImpThreads), 0, stream, attn, H, L, hpw,
                        n_norm, x, d, xvec, norms, partial);
   else
-    hipLaunchKernelGGL((importance_colsum_kernel<false>), cgrid, dim3(kImpThreads), 0, stream, attn, H, L, hpw,
+    hipLaunchKernelGGL((importance_colsum_kernel<false, false>), cgrid, dim3(kImpThreads), 0, stream, attn, H, L, hpw,
                        n_norm, x, d, xvec, norms, partial);
   timing_end(stream, kSiteImpColsum);
   hipError_t err = hipGetLastError();
