@@ -192,17 +192,21 @@ static int decode_splits(int K, int* c_per) {
 // prefill path).  Up to kDecodeMaxT tokens the GEMVs stream the weights
 // faster, but once per 16 pairs of an expert, and every piece of a matrix
 // costs a workgroup a set-up; the GEMMs stream them once per 32 pairs and pay
-// one more launch.  So the GEMMs take batches with 12 or more pairs an expert
-// (Mixtral layer at 32 tokens: GEMVs 124 us, GEMMs 136; 48: 143 and 146; 64:
-// 167 and 151), and from 12 tokens on the layers whose touched experts are
-// small (OLMoE layer, 403 M weights, at 16 tokens: 47.9 and 46.1 us, 32: 55 and
-// 49; 16 experts of 11 M weights, 16 tokens: 49 and 40; 60 of 21.5 M, 16
-// tokens: 61 and 68).  A small batch whose GEMM workspace would not fit the
+// one more launch, which routes too with up to 16 experts.  So the GEMMs take
+// batches with 12 or more pairs an expert (Mixtral layer at 32 tokens: GEMVs 124
+// us, GEMMs 136; 48: 143 and 146; 64: 167 and 151), and from 12 tokens on the
+// layers whose touched experts are small: with up to 16 experts up to 250 M
+// weights (even routing, 16 tokens: 16 experts of 12.6 M 38.3 and 35.6 us; of 25
+// M 47.2 and 53.7, skewed 37.9 and 38.1; 8 of 44 M 55.0 and 58.6), with more,
+// whose many half-empty m-tiles cost the GEMMs most where the routing is even,
+// up to 60 M (60 of 0.8 M: 31.8 and 30.6; 24 of 4.9 M: 34.2 and 35.5; OLMoE layer,
+// 64 of 6.3 M: 56.8 and 64.1, skewed 47.2 and 44.4; at 32 tokens 54.9 and 68.3,
+// 54.3 and 56.0).  A small batch whose GEMM workspace would not fit the
 // library's own scratch keeps the GEMVs.
 static bool use_decode(int T, int E, int k, int d, int ffn) {
   if (T > kDecodeMaxT) return false;
   const double touched = (double)(T * k < E ? T * k : E) * 3.0 * d * ffn;
-  const bool gemm = (double)T * k >= 12.0 * E || (T >= 12 && touched <= 450e6);
+  const bool gemm = (double)T * k >= 12.0 * E || (T >= 12 && touched <= (E <= 16 ? 250e6 : 60e6));
   return !gemm || prefill_workspace_bytes(T, E, k, d, ffn) > MC_NOALLOC_SCRATCH_BYTES;
 }
 
