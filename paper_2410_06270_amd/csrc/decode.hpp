@@ -67,6 +67,7 @@ struct DecodeArgs {
   int c_per;                  // chunks per split (the last split may be shorter)
   int gu_split;               // down: splits of the gate/up reduction (1: read h)
   int nwg;                    // workgroups in the grid
+  bool stream;                // weights by non-temporal loads (decode_streams)
 };
 
 // -------------------------------------------------------------- the plan --
@@ -211,12 +212,14 @@ __device__ __forceinline__ void cursor_next(DecCursor& k, const DecGeom& g, bool
 }
 
 // The lane's offset is the load's VGPR offset; the wave-uniform chunk offset
-// goes into the SGPR offset field, so a refill costs no vector adds.
-template <int BITS, int GPC>
+// goes into the SGPR offset field, so a refill costs no vector adds.  AUX:
+// the words' cache bits (the scale/zero words, 64 bytes of a 128-byte line at a
+// time, stay ordinary loads: streamed too, Mixtral layer, 32 tokens: 106 -> 108).
+template <int BITS, int GPC, int AUX>
 __device__ __forceinline__ void dec_load(uint32_t (&w)[2][BITS], uint32_t (&s)[2][GPC], const DecGeom& g,
                                          const DecCursor& k) {
 #pragma unroll
-  for (int j = 0; j < 2; ++j) load_words_so<BITS>(w[j], g.w, g.lane_w, g.bw[j] + k.wo);
+  for (int j = 0; j < 2; ++j) load_words_so<BITS, AUX>(w[j], g.w, g.lane_w, g.bw[j] + k.wo);
 #pragma unroll
   for (int q = 0; q < GPC; ++q)
 #pragma unroll
@@ -249,7 +252,7 @@ __device__ __forceinline__ int dec_part_start(int N, int D, int w, int nw) {
 // split over several waves.  Vector
 // memory stores happen only between row units (outside the unrolled ring), so
 // the compiler's load counting keeps the ring in flight.
-template <int BITS, int GPC, bool F16, int D, typename EarlyFn, typename LateFn, typename EmitFn>
+template <int BITS, int GPC, bool F16, int D, int AUX, typename EarlyFn, typename LateFn, typename EmitFn>
 __device__ __forceinline__ void decode_run(const DecGeom& g, int u0, int u1, int C, int w0, int w1,
                                            const uint16_t* arow, const float* sxs, float* tails,
                                            EarlyFn stage_early, LateFn stage_late, EmitFn emit) {
@@ -269,7 +272,7 @@ __device__ __forceinline__ void decode_run(const DecGeom& g, int u0, int u1, int
   if (qa < qb) {
 #pragma unroll
     for (int j = 0; j < D; ++j) {
-      dec_load<BITS, GPC>(wr[j], sr[j], g, pc);
+      dec_load<BITS, GPC, AUX>(wr[j], sr[j], g, pc);
       cursor_next(pc, g, pleft > 0);
       pleft = pleft > 0 ? pleft - 1 : 0;
     }
@@ -306,7 +309,7 @@ __device__ __forceinline__ void decode_run(const DecGeom& g, int u0, int u1, int
 #pragma unroll
       for (int j = 0; j < D; ++j) {
         compute_chunk<BITS, 1, GPC, F16>(wr[j], sr[j], acc, tot, ar, sxs, c + j, lane, magic);
-        dec_load<BITS, GPC>(wr[j], sr[j], g, pc);
+        dec_load<BITS, GPC, AUX>(wr[j], sr[j], g, pc);
         cursor_next(pc, g, pleft > 0);
         pleft = pleft > 0 ? pleft - 1 : 0;
         // the refill issues here, not later: left to itself the scheduler
@@ -370,7 +373,7 @@ __device__ __forceinline__ void decode_run(const DecGeom& g, int u0, int u1, int
 
 // One piece for an expert of width BITS: the streams' geometry, the staging
 // of its activations and the writing of its outputs, then decode_run.
-template <int BITS, int GPC, bool GATEUP>
+template <int BITS, int GPC, bool GATEUP, int AUX>
 __device__ __forceinline__ void decode_piece(const LayerArgs& L, const DecodeArgs& a, unsigned char* smem,
                                              const int32_t* s_tok, const DecPiece& p) {
   const int e = p.e, s = p.s, C = p.C, u0 = p.u0, u1 = p.u1, pbase = p.pbase, nt = p.nt;
@@ -507,11 +510,11 @@ __device__ __forceinline__ void decode_piece(const LayerArgs& L, const DecodeArg
   const int nchunks = (u1 - u0) * C, nwp = p.w1 - p.w0;
   const bool deep = DM == 2 || nchunks >= (nwp > 8 ? 4 : 3) * DM * nwp;
   if (C % DM == 0 && deep)
-    decode_run<BITS, GPC, F16, DM>(g, u0, u1, C, p.w0, p.w1, arow, sxs, tails, stage_early, stage_late, emit);
+    decode_run<BITS, GPC, F16, DM, AUX>(g, u0, u1, C, p.w0, p.w1, arow, sxs, tails, stage_early, stage_late, emit);
   else if (C % 2 == 0 && nchunks >= 2 * 2 * nwp)
-    decode_run<BITS, GPC, F16, 2>(g, u0, u1, C, p.w0, p.w1, arow, sxs, tails, stage_early, stage_late, emit);
+    decode_run<BITS, GPC, F16, 2, AUX>(g, u0, u1, C, p.w0, p.w1, arow, sxs, tails, stage_early, stage_late, emit);
   else
-    decode_run<BITS, GPC, F16, 1>(g, u0, u1, C, p.w0, p.w1, arow, sxs, tails, stage_early, stage_late, emit);
+    decode_run<BITS, GPC, F16, 1, AUX>(g, u0, u1, C, p.w0, p.w1, arow, sxs, tails, stage_early, stage_late, emit);
 }
 
 constexpr int kDecMaxPieces = 8;   // pieces planned per round (a share crosses few items)
@@ -588,7 +591,7 @@ __device__ __forceinline__ void plan_round(const LayerArgs& L, const DecodeArgs&
   }
 }
 
-template <int GPC, bool GATEUP, int NW>
+template <int GPC, bool GATEUP, int NW, int AUX>
 __global__ void __launch_bounds__(64 * NW) __attribute__((amdgpu_waves_per_eu(NW / 4)))
 decode_kernel(LayerArgs L, DecodeArgs a) {
   static_assert(NW >= 2 && NW <= kDecWaves, "waves of the decode workgroup");
@@ -632,11 +635,11 @@ decode_kernel(LayerArgs L, DecodeArgs a) {
         if (plan.piece[i].batch == bt && plan.piece[i].w0 <= wave && wave < plan.piece[i].w1) mine = i;
       const DecPiece p = plan.piece[mine];
       if (p.b == 1)
-        decode_piece<1, GPC, GATEUP>(L, a, smem, s_tok, p);
+        decode_piece<1, GPC, GATEUP, AUX>(L, a, smem, s_tok, p);
       else if (p.b == 2)
-        decode_piece<2, GPC, GATEUP>(L, a, smem, s_tok, p);
+        decode_piece<2, GPC, GATEUP, AUX>(L, a, smem, s_tok, p);
       else
-        decode_piece<3, GPC, GATEUP>(L, a, smem, s_tok, p);
+        decode_piece<3, GPC, GATEUP, AUX>(L, a, smem, s_tok, p);
     }
     if (!more) break;
     __syncthreads();                 // every wave has read the plan and left the slab
@@ -653,21 +656,40 @@ decode_kernel(LayerArgs L, DecodeArgs a) {
 // 8 waves win for gate/up up to 8 tokens, for down up to 4.
 inline int decode_waves(bool gateup, int T) { return T <= (gateup ? 8 : 4) ? 8 : 16; }
 
-template <int GPC, bool GATEUP, int NW>
+// Whether a batch's weights are read by non-temporal loads, which leave the
+// memory-side cache (256 MB) to other data.  Where a call touches more than
+// that cache keeps, allocating its stream there only costs: Mixtral layer
+// (485 MB), 8 tokens: 112 -> 98 us a call, 16: 115 -> 101, 32: 118 -> 106 (the
+// same with three layers rotated).  Where it touches less, the next call may
+// find it there: Mixtral layer at 4 tokens (331 MB) 58.5 -> 59.8 us repeated,
+// 61.6 -> 59.8 rotated; 8 experts of 11 M weights, 1 token 23.9 -> 25.5; 60 of
+// 21.5 M, 4 tokens 53.8 -> 63.5.  Bytes of the experts
+// an even routing touches, against one and a half times the cache.
+inline bool decode_streams(const LayerArgs& L, int T, int k) {
+  const double touched = 1.0 - pow(1.0 - (double)k / L.E, (double)T);
+  const double bytes = 3.0 * L.d * L.ffn * (L.cum_bits[L.E] / 8.0 + 4.0 * L.E / L.G);
+  return touched * bytes >= 384e6;
+}
+
+template <int GPC, bool GATEUP, int NW, int AUX>
 hipError_t launch_decode_nw(const LayerArgs& L, const DecodeArgs& a, hipStream_t stream) {
   constexpr int lds = kDecSlabBytes + kDecSumBytes;
   // set once per instantiation (thread-safe static initialisation)
-  static const hipError_t attr = hipFuncSetAttribute(
-      reinterpret_cast<const void*>(&decode_kernel<GPC, GATEUP, NW>), hipFuncAttributeMaxDynamicSharedMemorySize, lds);
+  static const hipError_t attr =
+      hipFuncSetAttribute(reinterpret_cast<const void*>(&decode_kernel<GPC, GATEUP, NW, AUX>),
+                          hipFuncAttributeMaxDynamicSharedMemorySize, lds);
   if (attr != hipSuccess) return attr;
-  hipLaunchKernelGGL((decode_kernel<GPC, GATEUP, NW>), dim3(a.nwg), dim3(64 * NW), lds, stream, L, a);
+  hipLaunchKernelGGL((decode_kernel<GPC, GATEUP, NW, AUX>), dim3(a.nwg), dim3(64 * NW), lds, stream, L, a);
   return hipGetLastError();
 }
 
 template <int GPC, bool GATEUP>
 hipError_t launch_decode(const LayerArgs& L, const DecodeArgs& a, hipStream_t stream) {
-  return decode_waves(GATEUP, a.T) == 8 ? launch_decode_nw<GPC, GATEUP, 8>(L, a, stream)
-                                        : launch_decode_nw<GPC, GATEUP, 16>(L, a, stream);
+  if (decode_waves(GATEUP, a.T) == 8)
+    return a.stream ? launch_decode_nw<GPC, GATEUP, 8, kNonTemporal>(L, a, stream)
+                    : launch_decode_nw<GPC, GATEUP, 8, 0>(L, a, stream);
+  return a.stream ? launch_decode_nw<GPC, GATEUP, 16, kNonTemporal>(L, a, stream)
+                  : launch_decode_nw<GPC, GATEUP, 16, 0>(L, a, stream);
 }
 
 }  // namespace mc

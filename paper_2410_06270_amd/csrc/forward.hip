@@ -340,6 +340,7 @@ hipError_t launch_expert_partials(const uint16_t* x, const LayerArgs& L, const m
   a.T = T;
   a.P = (int)P;
   a.nwg = device_cus();
+  a.stream = decode_streams(L, T, k);
   int c_gu = 0, c_dn = 0;
   const int s_gu = decode_splits(L.d, &c_gu);
   const int nsplit = decode_splits(L.ffn, &c_dn);

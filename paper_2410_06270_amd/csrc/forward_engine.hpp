@@ -131,17 +131,19 @@ __device__ __forceinline__ void load_words(uint32_t (&w)[BITS], rsrc_t r, uint32
   }
 }
 
-// As load_words, with a VGPR offset (the lane's) and an SGPR offset (wave-uniform).
-template <int BITS>
+// As load_words, with a VGPR offset (the lane's) and an SGPR offset
+// (wave-uniform); AUX: the load's cache bits (0, or kNonTemporal).
+constexpr int kNonTemporal = 2;
+template <int BITS, int AUX = 0>
 __device__ __forceinline__ void load_words_so(uint32_t (&w)[BITS], rsrc_t r, uint32_t voff, uint32_t soff) {
   if constexpr (BITS == 1) {
-    w[0] = __builtin_amdgcn_raw_buffer_load_b32(r, voff, soff, 0);
+    w[0] = __builtin_amdgcn_raw_buffer_load_b32(r, voff, soff, AUX);
   } else if constexpr (BITS == 2) {
-    const auto v = __builtin_amdgcn_raw_buffer_load_b64(r, voff, soff, 0);
+    const auto v = __builtin_amdgcn_raw_buffer_load_b64(r, voff, soff, AUX);
     w[0] = v[0];
     w[1] = v[1];
   } else {
-    const auto v = __builtin_amdgcn_raw_buffer_load_b96(r, voff, soff, 0);
+    const auto v = __builtin_amdgcn_raw_buffer_load_b96(r, voff, soff, AUX);
     w[0] = v[0];
     w[1] = v[1];
     w[2] = v[2];
