@@ -415,8 +415,8 @@ mc_status mc_pmq_expert_error(const float* w_gate, const float* w_up, const floa
   mc_status s = check_routing(r);
   if (s != MC_OK) return s;
   if (r->E != E) return fail(MC_EINVAL, "routing has E=%d, the weights E=%d", r->E, E);
-  size_t need = 0;
-  s = mc_pmq_error_workspace(r->T, E, r->k, d, ffn, group, &need);
+  const std::vector<int> three(E, 3);
+  s = check_shape(E, d, ffn, three.data(), group);
   if (s != MC_OK) return s;
   if (!w_gate || !w_up || !w_down || !x_bf16 || !eps_host || !workspace)
     return fail(MC_EINVAL, "weight, x, eps or workspace pointer is NULL");

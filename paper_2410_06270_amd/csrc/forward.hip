@@ -203,11 +203,15 @@ static int decode_splits(int K, int* c_per) {
 // 64 of 6.3 M: 56.8 and 64.1, skewed 47.2 and 44.4; at 32 tokens 54.9 and 68.3,
 // 54.3 and 56.0).  A small batch whose GEMM workspace would not fit the
 // library's own scratch keeps the GEMVs.
-static bool use_decode(int T, int E, int k, int d, int ffn) {
-  if (T > kDecodeMaxT) return false;
+static bool gemms_pay(int T, int E, int k, int d, int ffn) {
+  if (T > kDecodeMaxT) return true;
   const double touched = (double)(T * k < E ? T * k : E) * 3.0 * d * ffn;
-  const bool gemm = (double)T * k >= 12.0 * E || (T >= 12 && touched <= (E <= 16 ? 250e6 : 60e6));
-  return !gemm || prefill_workspace_bytes(T, E, k, d, ffn) > MC_NOALLOC_SCRATCH_BYTES;
+  return (double)T * k >= 12.0 * E || (T >= 12 && touched <= (E <= 16 ? 250e6 : 60e6));
+}
+
+static bool use_decode(int T, int E, int k, int d, int ffn) {
+  return !gemms_pay(T, E, k, d, ffn) ||
+         (T <= kDecodeMaxT && prefill_workspace_bytes(T, E, k, d, ffn) > MC_NOALLOC_SCRATCH_BYTES);
 }
 
 // Compute units of the current device (one decode workgroup each).
@@ -228,7 +232,10 @@ static int device_cus() {
 static size_t round256(size_t b) { return ((b + 255) / 256) * 256; }
 
 size_t forward_workspace_bytes(int T, int E, int k, int d, int ffn) {
-  if (!use_decode(T, E, k, d, ffn)) return prefill_workspace_bytes(T, E, k, d, ffn);
+  if (gemms_pay(T, E, k, d, ffn)) {   // use_decode, with its workspace at hand
+    const size_t gemm = prefill_workspace_bytes(T, E, k, d, ffn);
+    if (T > kDecodeMaxT || gemm <= MC_NOALLOC_SCRATCH_BYTES) return gemm;
+  }
   const size_t P = (size_t)T * k;
   const int ks = decode_splits(d, nullptr);
   const size_t h = round256(P * ffn * sizeof(uint16_t));
@@ -243,8 +250,8 @@ size_t forward_workspace_bytes(int T, int E, int k, int d, int ffn) {
 // whose GEMM workspace is too large keeps the GEMVs, whose own is small.
 size_t forward_workspace_upto(int T, int E, int k, int d, int ffn) {
   size_t most = 0;
-  for (int t = 1; t <= T; ++t) most = std::max(most, forward_workspace_bytes(t, E, k, d, ffn));
-  return most;
+  for (int t = 1; t <= T && t <= kDecodeMaxT; ++t) most = std::max(most, forward_workspace_bytes(t, E, k, d, ffn));
+  return T > kDecodeMaxT ? std::max(most, prefill_workspace_upto(kDecodeMaxT + 1, T, E, k, d, ffn)) : most;
 }
 
 size_t routing_set_bytes(int T, int E, int k) {
@@ -283,10 +290,12 @@ size_t stack_workspace_bytes(int T, int E, int k, int d, int ffn) {
 }
 
 size_t stack_workspace_upto(int T, int E, int k, int d, int ffn) {
-  // at least the parts of T beside the largest forward workspace
+  // the parts of T beside the largest forward workspace; of the smaller batches
+  // only those that route their layers side by side may have larger parts
+  static_assert(kRouteFusedMaxT <= kDecodeMaxT, "batches routed side by side are small");
   size_t most = stack_workspace_bytes(T, E, k, d, ffn) - forward_workspace_bytes(T, E, k, d, ffn) +
                 forward_workspace_upto(T, E, k, d, ffn);
-  for (int t = 1; t < T; ++t) most = std::max(most, stack_workspace_bytes(t, E, k, d, ffn));
+  for (int t = 1; t < T && t <= kDecodeMaxT; ++t) most = std::max(most, stack_workspace_bytes(t, E, k, d, ffn));
   return most;
 }
 

@@ -66,6 +66,8 @@ struct PrefillLayout {
 };
 PrefillLayout prefill_layout(int T, int E, int k, int d, int ffn, int G);
 size_t prefill_workspace_bytes(int T, int E, int k, int d, int ffn);
+// At least that of every batch of lo to T tokens, monotone in T.
+size_t prefill_workspace_upto(int lo, int T, int E, int k, int d, int ffn);
 // Routing inputs of a forward call that routes its batch first (the outputs
 // go to the mc_routing buffers as mc_route_and_prune writes them).
 struct RouteArgs {

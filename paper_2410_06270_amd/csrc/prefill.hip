@@ -267,31 +267,51 @@ static int prefill_rows(int tiles, int G, bool gateup) {
                                                                : prefill_rows_g<4>(tiles, gateup);
 }
 
-PrefillLayout prefill_layout(int T, int E, int k, int d, int ffn, int G) {
+// What the down reduction's splits follow: its row blocks, the workgroups at
+// once and the most splits (at least 8 chunks in each).
+struct PrefillSplit {
+  int tiles, nt_down, slots, most;
+};
+static PrefillSplit prefill_split(int tiles, int d, int ffn, int G) {
+  const int rows = prefill_rows(tiles, G, false), most = (ffn / kTileCols) / 8;
+  return {tiles, (d + rows - 1) / rows, 256 * (tiles == 4 ? 1 : tiles == 2 ? (G == 128 ? 2 : 3) : 4),
+          most < 1 ? 1 : most < 4 ? most : 4};
+}
+
+static int prefill_mt_max(int tiles, int T, int E, int k) {
+  const size_t mtok = (size_t)tiles * kPfFragRows;
+  return (int)(((size_t)T * k + (mtok - 1) * E) / mtok);
+}
+
+// The m-tiles that the splits are chosen for: the small tiles' count is about
+// those in use.
+static long long prefill_mt_planned(int tiles, int T, int E, int k) {
+  const long long mt = prefill_mt_max(tiles, T, E, k);
+  if (tiles == 4) return mt;
+  const double per = (double)T * k / E / (tiles * kPfFragRows);
+  const long long est = (long long)(E * (per < 0.5 ? 1.0 : per + 0.5));
+  return est < mt ? est : mt;
+}
+
+// Splits of the down GEMM's reduction, so that its workgroups fill the CUs in
+// whole rounds: the s minimising rounds(s) / s (the time of one round shrinks
+// as 1/s), the smallest on ties.  It depends on mt * nt_down modulo the slots
+// only.
+static int prefill_nsplit(const PrefillSplit& p, long long mt) {
+  const long long wgs = mt * p.nt_down;
+  int s = 1;
+  for (int c = 2; c <= p.most; ++c)
+    if ((double)((wgs * c + p.slots - 1) / p.slots) / c < (double)((wgs * s + p.slots - 1) / p.slots) / s - 1e-9) s = c;
+  return s;
+}
+
+// The layout with no down partials yet (total = part).
+static PrefillLayout prefill_layout_base(int tiles, int T, int E, int k, int d, int ffn) {
   PrefillLayout pl;
   const size_t P = (size_t)T * k;
   pl.f_max = (int)((P + (size_t)(kPfFragRows - 1) * E) / kPfFragRows);
-  pl.tiles = prefill_tiles(T, E, k, d, ffn);
-  const size_t mtok = (size_t)pl.tiles * kPfFragRows;
-  pl.mt_max = (int)((P + (mtok - 1) * E) / mtok);
-  // Split the down GEMM's reduction so that its workgroups fill the CUs in
-  // whole rounds: pick s minimising rounds(s) / s (the time of one round
-  // shrinks as 1/s), the smallest on ties; at least 8 chunks per split.
-  const int rows_down = prefill_rows(pl.tiles, G, false);
-  const int nt_down = (d + rows_down - 1) / rows_down;
-  const int slots = 256 * (pl.tiles == 4 ? 1 : pl.tiles == 2 ? (G == 128 ? 2 : 3) : 4);   // workgroups at once
-  long long mt = pl.mt_max;
-  if (pl.tiles < 4) {   // about the m-tiles in use
-    const double per = (double)P / E / mtok;
-    const long long est = (long long)(E * (per < 0.5 ? 1.0 : per + 0.5));
-    if (est < mt) mt = est;
-  }
-  const long long wgs = mt * nt_down;
-  int maxs = (ffn / kTileCols) / 8;
-  if (maxs > 4) maxs = 4;
-  int s = 1;
-  for (int c = 2; c <= maxs; ++c)
-    if ((double)((wgs * c + slots - 1) / slots) / c < (double)((wgs * s + slots - 1) / slots) / s - 1e-9) s = c;
+  pl.tiles = tiles;
+  pl.mt_max = prefill_mt_max(tiles, T, E, k);
   // the GEMMs stage whole m-tiles: tiles - 1 padding fragment rows past the last one
   const size_t rows = (size_t)(pl.f_max + pl.tiles) * kPfFragRows;
   pl.tables = 0;
@@ -301,8 +321,19 @@ PrefillLayout prefill_layout(int T, int E, int k, int d, int ffn, int G) {
   pl.h = pl.xsum + round256(rows * (d / 32) * sizeof(float));   // G >= 32
   pl.hsum = pl.h + round256(rows * ffn * sizeof(uint16_t));
   pl.part = pl.hsum + round256(rows * (ffn / 32) * sizeof(float));
+  pl.total = pl.part;
+  pl.nsplit = 0;
+  return pl;
+}
+
+static size_t prefill_split_bytes(int T, int k, int d) { return (size_t)T * k * d * sizeof(float); }
+
+PrefillLayout prefill_layout(int T, int E, int k, int d, int ffn, int G) {
+  const int tiles = prefill_tiles(T, E, k, d, ffn);
+  PrefillLayout pl = prefill_layout_base(tiles, T, E, k, d, ffn);
+  int s = prefill_nsplit(prefill_split(tiles, d, ffn, G), prefill_mt_planned(tiles, T, E, k));
   // a batch that fits the library's own scratch with fewer splits takes those
-  const size_t split = P * d * sizeof(float);
+  const size_t split = prefill_split_bytes(T, k, d);
   if (pl.part + s * split > MC_NOALLOC_SCRATCH_BYTES && pl.part + split <= MC_NOALLOC_SCRATCH_BYTES)
     s = (int)((MC_NOALLOC_SCRATCH_BYTES - pl.part) / split);
   pl.nsplit = s;
@@ -314,6 +345,56 @@ PrefillLayout prefill_layout(int T, int E, int k, int d, int ffn, int G) {
 size_t prefill_workspace_bytes(int T, int E, int k, int d, int ffn) {
   return std::max({prefill_layout(T, E, k, d, ffn, 32).total, prefill_layout(T, E, k, d, ffn, 64).total,
                    prefill_layout(T, E, k, d, ffn, 128).total});
+}
+
+// The smallest T in (lo, hi] that satisfies f, hi if none before it does; f
+// does not turn false again as T grows.
+template <typename F>
+static int first_T(int lo, int hi, F f) {
+  while (hi - lo > 1) {
+    const int mid = lo + (hi - lo) / 2;
+    if (f(mid)) hi = mid;
+    else lo = mid;
+  }
+  return hi;
+}
+
+// The largest prefill_workspace_bytes of the batches of lo to T tokens, without
+// walking them all.  For one m-tile size and one number of splits the layout
+// grows with T, so only the last T of each pair counts, and the splits repeat
+// with the m-tile count's residue: at most `slots` counts back from the end of
+// an m-tile size's range every number of splits has been met.  (The three
+// layouts of every T up to 65536 took 14 ms.)  Batches that fit the scratch
+// with one split need no more than it, however many they would take otherwise,
+// and fewer bytes than one that does not fit.
+size_t prefill_workspace_upto(int lo, int T, int E, int k, int d, int ffn) {
+  const size_t scratch = MC_NOALLOC_SCRATCH_BYTES;
+  const auto one_split = [&](int t) {
+    return prefill_layout_base(prefill_tiles(t, E, k, d, ffn), t, E, k, d, ffn).total + prefill_split_bytes(t, k, d);
+  };
+  const bool in_scratch = one_split(T) <= scratch;
+  if (!in_scratch && one_split(lo) <= scratch) lo = first_T(lo, T, [&](int t) { return one_split(t) > scratch; });
+  size_t most = 0;
+  for (int end = T; end >= lo;) {
+    const int tiles = prefill_tiles(end, E, k, d, ffn);
+    const auto same = [&](int t) { return prefill_tiles(t, E, k, d, ffn) >= tiles; };
+    const int begin = same(lo) ? lo : first_T(lo, end, same);
+    for (int G = 32; G <= 128; G *= 2) {
+      const PrefillSplit sp = prefill_split(tiles, d, ffn, G);
+      int met = 0;
+      for (int t = end, n = 0; t >= begin && met < sp.most && n < sp.slots; ++n) {
+        const long long mt = prefill_mt_planned(tiles, t, E, k);
+        const int s = prefill_nsplit(sp, mt);
+        if (s > met) {
+          met = s;
+          most = std::max(most, prefill_layout_base(tiles, t, E, k, d, ffn).total + s * prefill_split_bytes(t, k, d));
+        }
+        t = first_T(begin - 1, t, [&](int u) { return prefill_mt_planned(tiles, u, E, k) >= mt; }) - 1;
+      }
+    }
+    end = begin - 1;
+  }
+  return in_scratch ? std::min(most, scratch) : most;
 }
 
 hipError_t launch_prefill(const uint16_t* x, const LayerArgs& L, const mc_routing& r, void* ws,

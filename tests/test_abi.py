@@ -153,6 +153,35 @@ def test_workspace_serves_smaller_batches(lib, query, shape):
     assert sizes == sorted(sizes)
 
 
+@pytest.mark.parametrize("shape", [(8, 2, 4096, 14336), (64, 8, 2048, 1024), (60, 2, 1024, 4096), (4, 2, 256, 512),
+                                   (1, 1, 128, 128), (256, 8, 128, 128), (3, 1, 16384, 1024), (16, 4, 2432, 2944)])
+def test_workspace_is_the_largest_need(lib, shape):
+    """mc_forward_workspace(T) is the largest need of any batch of up to T
+    tokens (up to the library's own scratch of 32 MiB it may answer that
+    instead), found without walking the batches: 65536 tokens in well under a
+    millisecond (one layout for each would take more than ten)."""
+    import time
+    need = lib["_ZN2mc23forward_workspace_bytesEiiiii"]      # a batch's own
+    need.restype, need.argtypes = ctypes.c_size_t, [ctypes.c_int] * 5
+    b = ctypes.c_size_t()
+    ask = {*range(1, 200), *range(200, 8192, 37), 8192}
+    most = 0
+    for T in range(1, 8193):
+        most = max(most, need(T, *shape))
+        if T in ask:
+            assert lib.mc_forward_workspace(T, *shape, ctypes.byref(b)) == 0
+            assert most <= b.value <= max(most, 32 << 20), T
+    for fn in (lib.mc_forward_workspace, lib.mc_stack_workspace):
+        t = min(_timed(lambda: fn(65536, *shape, ctypes.byref(b)), time.perf_counter) for _ in range(20))
+        assert t < 1e-3, (fn, t)
+
+
+def _timed(f, clock):
+    t = clock()
+    f()
+    return clock() - t
+
+
 def test_stack_workspace(lib):
     """mc_stack_workspace = the normalised input + (batches routed by one
     workgroup: T <= 64 and T <= 16*64/S) the routing buffers of 8 layers +
