@@ -230,6 +230,18 @@ bool prefill_routes(int T, int E) { return E <= 16 && route_fused_fits(T, E); }
 
 static size_t round256(size_t b) { return ((b + 255) / 256) * 256; }
 
+// The most m-tiles of a batch: every expert's last one may be short.
+static int prefill_mt_max(int tiles, int T, int E, int k) {
+  const size_t mtok = (size_t)tiles * kPfFragRows;
+  return (int)(((size_t)T * k + (mtok - 1) * E) / mtok);
+}
+
+// The most splits of the down reduction: at least 8 chunks in each.
+static int prefill_most_splits(int ffn) {
+  const int most = (ffn / kTileCols) / 8;
+  return most < 1 ? 1 : most < 4 ? most : 4;
+}
+
 // Fragment rows of the m-tiles.  Larger m-tiles unpack (and read) the weights
 // less often, smaller ones keep more workgroups on a CU and leave less padding
 // and a shorter last round, so the choice follows the pairs an expert sees and
@@ -248,11 +260,16 @@ static size_t round256(size_t b) { return ((b + 255) / 256) * 256; }
 // in a short run the 64-token ones are faster there too (Mixtral, 4096 tokens:
 // 2468 against 2573 us), but under sustained load, where the card's power sets
 // the clock, the extra unpacking costs more than it hides (2889 against 2867).
+// A launch holds fewer than 2^32 threads, four a row of gate/up and two a row
+// of down: where small m-tiles would need more, larger ones are taken.
 static int prefill_tiles(int T, int E, int k, int d, int ffn) {
   const double per = (double)T * k / E;
   const double wgs2 = E * (per / 64 + 0.5) * ffn / 128;     // gate/up workgroups of 64-token m-tiles
-  if (per <= 36 || wgs2 < 1000) return 1;
-  return per >= 512 && wgs2 >= 7000 && d >= 2048 && ffn >= 2048 ? 4 : 2;
+  int tiles = per >= 512 && wgs2 >= 7000 && d >= 2048 && ffn >= 2048 ? 4 : 2;
+  if (per <= 36 || wgs2 < 1000) tiles = 1;
+  const double threads = std::max(4.0 * ffn, 2.0 * (d + 256.0) * prefill_most_splits(ffn));   // of an m-tile
+  while (tiles < 4 && prefill_mt_max(tiles, T, E, k) * threads >= 4294967296.0) tiles *= 2;
+  return tiles;
 }
 
 // Weight rows of a workgroup (ffn rows of gate/up, d rows of down).
@@ -268,19 +285,14 @@ static int prefill_rows(int tiles, int G, bool gateup) {
 }
 
 // What the down reduction's splits follow: its row blocks, the workgroups at
-// once and the most splits (at least 8 chunks in each).
+// once and the most splits.
 struct PrefillSplit {
   int tiles, nt_down, slots, most;
 };
 static PrefillSplit prefill_split(int tiles, int d, int ffn, int G) {
-  const int rows = prefill_rows(tiles, G, false), most = (ffn / kTileCols) / 8;
+  const int rows = prefill_rows(tiles, G, false);
   return {tiles, (d + rows - 1) / rows, 256 * (tiles == 4 ? 1 : tiles == 2 ? (G == 128 ? 2 : 3) : 4),
-          most < 1 ? 1 : most < 4 ? most : 4};
-}
-
-static int prefill_mt_max(int tiles, int T, int E, int k) {
-  const size_t mtok = (size_t)tiles * kPfFragRows;
-  return (int)(((size_t)T * k + (mtok - 1) * E) / mtok);
+          prefill_most_splits(ffn)};
 }
 
 // The m-tiles that the splits are chosen for: the small tiles' count is about

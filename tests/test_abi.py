@@ -182,6 +182,33 @@ def _timed(f, clock):
     return clock() - t
 
 
+class _PrefillLayout(ctypes.Structure):
+    _fields_ = [(n, ctypes.c_size_t) for n in ("tables", "x", "xsum", "h", "hsum", "part", "total")] + \
+               [(n, ctypes.c_int) for n in ("f_max", "mt_max", "nsplit", "tiles")]
+
+
+@pytest.mark.parametrize("T,E,k,d,ffn", [
+    (65536, 8, 8, 1024, 131072),      # 64-token m-tiles: 4.30e9 threads of gate/up
+    (65536, 8, 8, 1024, 130816),      # the largest ffn whose 64-token ones fit
+    (144, 32, 8, 128, 1 << 24),       # 32-token ones: 4.56e9
+    (65536, 64, 8, 2048, 16384), (4096, 8, 2, 4096, 14336),
+])
+@pytest.mark.parametrize("G", [32, 64, 128])
+def test_prefill_grids_fit_a_launch(lib, G, T, E, k, d, ffn):
+    """The GEMMs' grids stay below the 2^32 threads of a launch wherever those
+    of the 128-token m-tiles do, whatever m-tile the sizes would take."""
+    layout = lib["_ZN2mc14prefill_layoutEiiiiii"]
+    layout.restype, layout.argtypes = _PrefillLayout, [ctypes.c_int] * 6
+    pl = layout(T, E, k, d, ffn, G)
+    assert (T * k + 127 * E) // 128 * max(4 * ffn, 2 * (d + 255) * pl.nsplit) < 2 ** 32
+    waves = 4 if pl.tiles == 1 or (pl.tiles == 2 and G < 128) else 8
+    gateup = pl.mt_max * (ffn // (32 * waves // 2)) * 64 * waves
+    down = pl.mt_max * -(-d // (32 * waves)) * pl.nsplit * 64 * waves
+    assert gateup < 2 ** 32 and down < 2 ** 32
+    if ffn == 130816:
+        assert pl.tiles == 2
+
+
 def test_stack_workspace(lib):
     """mc_stack_workspace = the normalised input + (batches routed by one
     workgroup: T <= 64 and T <= 16*64/S) the routing buffers of 8 layers +
