@@ -499,12 +499,19 @@ size_t gptq_quantize_bytes(int R, int K) {
   return (size_t)R * K * sizeof(double) + (((size_t)R * K + 255) / 256) * 256;
 }
 
-// Row r = blockIdx.x: fp64 weights, dead inputs 0; the row's loss starts at 0.
+// A row per workgroup at a time: fp64 weights, dead inputs 0; the row's loss
+// starts at 0.  The grid is capped: 2^24 rows of 256 threads are one more than
+// a launch holds.
+constexpr int kPrepRows = 1 << 20;
+
 __global__ void __launch_bounds__(256) gptq_prep_kernel(const float* __restrict__ W, const uint8_t* __restrict__ dead,
-                                                        int K, double* __restrict__ Ww, double* __restrict__ loss) {
-  const size_t o = (size_t)blockIdx.x * K;
-  for (int k = threadIdx.x; k < K; k += 256) Ww[o + k] = dead[k] ? 0.0 : (double)W[o + k];
-  if (loss && threadIdx.x == 0) loss[blockIdx.x] = 0.0;
+                                                        int R, int K, double* __restrict__ Ww,
+                                                        double* __restrict__ loss) {
+  for (int r = blockIdx.x; r < R; r += gridDim.x) {
+    const size_t o = (size_t)r * K;
+    for (int k = threadIdx.x; k < K; k += 256) Ww[o + k] = dead[k] ? 0.0 : (double)W[o + k];
+    if (loss && threadIdx.x == 0) loss[r] = 0.0;
+  }
 }
 
 __device__ __forceinline__ void quad_min_max(float& mn, float& mx) {
@@ -820,7 +827,7 @@ hipError_t launch_gptq_quantize(const float* W, const double* U, const uint8_t* 
   double* Ww = static_cast<double*>(ws);
   uint8_t* q = reinterpret_cast<uint8_t*>(Ww + (size_t)R * K);
   timing_begin(st, kSiteGptqQuantize);
-  hipLaunchKernelGGL(gptq_prep_kernel, dim3(R), dim3(256), 0, st, W, dead, K, Ww, loss);
+  hipLaunchKernelGGL(gptq_prep_kernel, dim3(R < kPrepRows ? R : kPrepRows), dim3(256), 0, st, W, dead, R, K, Ww, loss);
 #define MC_QUANT(B)                                                        \
   if (G == 32) quantize_blocks<B, 32>(Ww, U, R, K, q, words, sz, loss, st); \
   else if (G == 64) quantize_blocks<B, 64>(Ww, U, R, K, q, words, sz, loss, st); \

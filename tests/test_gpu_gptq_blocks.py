@@ -49,9 +49,34 @@ def test_quantize_blocks_bit_exact(R, K, bits, G):
     np.testing.assert_array_equal(got[same], want[same])
 
 
+def test_quantize_most_rows():
+    """The most rows the entry point takes (R K = 2^31): the first and last rows
+    as in a call of their own (rows are independent)."""
+    import paper_2410_06270_amd as mc
+    R, K, G = 1 << 24, 128, 128
+    U, dead = oracle.gptq_factor(oracle.gptq_hessian(synthetic.calibration(1, 2 * K, K, tag=K)))
+    U, dead = to_dev(U), to_dev(dead)
+    W = torch.randn((R, K), generator=torch.Generator(device="cuda").manual_seed(R), device="cuda").mul_(0.02)
+
+    def quantize(w):
+        n = w.shape[0]
+        L = mc.PackedLayer(1, K, n, [1], G)
+        ws = torch.empty(mc.gptq_workspace(n, K), dtype=torch.uint8, device="cuda")
+        loss = torch.empty(n, dtype=torch.float64, device="cuda")
+        mc.gptq_quantize(L, 0, 0, w, U, dead, ws, loss=loss)
+        torch.cuda.synchronize()
+        return L.words.view(torch.int32)[:n * K // 32], L.sz.view(torch.int32)[:n], loss
+
+    every = quantize(W)
+    for rows in (slice(0, 128), slice(R - 128, R)):
+        for big, small, per in zip(every, quantize(W[rows].contiguous()), (K // 32, 1, 1)):
+            assert torch.equal(big[rows.start * per:rows.stop * per], small)
+
+
 def test_quantize_infinite_weight():
-    """An infinite weight in the last column: its error, and so the row's loss,
-    is infinite (a division's, not a NaN); the other rows are untouched."""
+    """An infinite weight of either sign in the last column: its error, and so
+    the row's loss, is infinite (a division's, not a NaN); the other rows are
+    untouched."""
     import paper_2410_06270_amd as mc
     R, K, G = 128, 128, 32
     W = np.random.default_rng(3).standard_normal((R, K)).astype(np.float32) * np.float32(0.02)
@@ -64,7 +89,7 @@ def test_quantize_infinite_weight():
     mc.gptq_quantize(L, 0, 0, to_dev(W), to_dev(U), to_dev(dead), ws, loss=loss)
     torch.cuda.synchronize()
     loss = loss.cpu().numpy()
-    assert loss[5] == np.inf
+    assert loss[5] == np.inf and loss[9] == np.inf
     rows = [r for r in range(R) if r not in (5, 9)]
     want = oracle.gptq_quantize_u(W[rows], U, dead, 2, G)[3]
     np.testing.assert_allclose(loss[rows], want, rtol=1e-12)
