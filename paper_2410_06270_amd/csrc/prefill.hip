@@ -160,16 +160,15 @@ __global__ void __launch_bounds__(64 * kRouteWaves) route_prep_kernel(
     const float* __restrict__ logits, const uint8_t* __restrict__ important, int T, int E, int k, float delta32,
     double tau, RouteBufs o, const uint16_t* __restrict__ x, int d, PrefillTables tb, uint16_t* __restrict__ xt,
     float* __restrict__ xsum) {
-  __shared__ RouteSmallLds s;
-  static_assert(kPfFragRows * kGatherStride * 2 <= (int)sizeof(s.scratch), "the gather tile reuses the scratch");
+  static_assert(kPfFragRows * kGatherStride * 2 <= kRouteWaves * kSelScratchBytes, "the gather tile reuses the scratch");
   static_assert(kPfFragRows == 2 * kRouteWaves, "two rows a wave");
   const int lane = threadIdx.x & 63, wave = wave_id();
   const int f = blockIdx.x;
   const bool first = blockIdx.x == 0 && blockIdx.y == 0;
-  route_small_batch(s, logits, important, T, E, k, delta32, tau, o, first);
+  const RouteSmall s = route_small_batch(logits, important, T, E, k, delta32, tau, o, first);
   __syncthreads();
   // tables: lane e of every wave holds expert e (prefill_routes: E <= 16)
-  const int nf = lane < E ? (s.cnt[lane] + kPfFragRows - 1) / kPfFragRows : 0;
+  const int nf = lane < E ? (s.lists.cnt[lane] + kPfFragRows - 1) / kPfFragRows : 0;
   const int nm = (nf + tb.tiles - 1) / tb.tiles;
   int sf = nf, sm = nm;
 #pragma unroll
@@ -198,14 +197,14 @@ __global__ void __launch_bounds__(64 * kRouteWaves) route_prep_kernel(
   const int e = __builtin_ctzll(__ballot(fb <= f && f < fb + nf));   // exactly one expert holds f
   const int r0 = kPfFragRows * (f - __builtin_amdgcn_readlane(fb, e));
   // lane t: token t's place in e's list
-  const unsigned long long mask = s.bal[e];
+  const unsigned long long mask = s.lists.bal[e];
   const bool on_list = (mask >> lane) & 1ull;
   const int place = __popcll(mask & ((1ull << lane) - 1ull));
   const int c0 = blockIdx.y * kGatherCols;
   const int w = (d - c0) < kGatherCols ? (d - c0) : kGatherCols;   // a multiple of 128
   const bool on = 8 * lane < w;
   const int ng = d / (8 * GP);
-  uint16_t* tile = reinterpret_cast<uint16_t*>(&s.scratch[0][0]);   // the selections are done
+  uint16_t* tile = reinterpret_cast<uint16_t*>(s.scratch);   // the selections are done
 #pragma unroll
   for (int j = 0; j < 2; ++j) {
     const int m = 2 * wave + j;

@@ -120,8 +120,7 @@ __global__ void __launch_bounds__(kCsrThreads) route_scatter_kernel(
 __global__ void __launch_bounds__(kCsrThreads) route_fused_kernel(
     const float* __restrict__ logits, const uint8_t* __restrict__ important, int T, int E, int k,
     float delta32, double tau, RouteBufs o) {
-  __shared__ RouteSmallLds s;
-  route_small_batch(s, logits, important, T, E, k, delta32, tau, o, true);
+  route_small_batch(logits, important, T, E, k, delta32, tau, o, true);
 }
 
 // Several batches of the same shape at once, one workgroup each: batch b's
@@ -131,8 +130,7 @@ __global__ void __launch_bounds__(kCsrThreads) route_fused_batch_kernel(
     const float* __restrict__ logits, const uint8_t* __restrict__ important, int T, int E, int k,
     float delta32, double tau, RouteBatch o) {
   const size_t b = blockIdx.x;
-  __shared__ RouteSmallLds s;
-  route_small_batch(s, logits + b * T * E, important ? important + b * T : nullptr, T, E, k, delta32, tau, o.r[b],
+  route_small_batch(logits + b * T * E, important ? important + b * T : nullptr, T, E, k, delta32, tau, o.r[b],
                     true);
 }
 

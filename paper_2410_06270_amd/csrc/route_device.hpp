@@ -280,39 +280,45 @@ __host__ __device__ constexpr bool route_fused_fits(int T, int E) {
   return T <= kRouteFusedMaxT && (E <= 64 ? T <= kRouteWaves * (64 / sel_segment(E)) : T * E <= 512);
 }
 
-struct RouteSmallLds {
-  __attribute__((aligned(16))) unsigned char scratch[kRouteWaves][kSelScratchBytes];
-  unsigned long long bal[MC_MAX_EXPERTS];
-  uint16_t ent[kRouteFusedMaxT * MC_MAX_TOPK];
-  float wsel[kRouteFusedMaxT * MC_MAX_TOPK];
-  int cnt[MC_MAX_EXPERTS];
-  int base[MC_MAX_EXPERTS + 1];
+// What the small-batch routing leaves in LDS.
+struct RouteSmall {
+  RouteLds lists;
+  unsigned char* scratch;    // kRouteWaves * kSelScratchBytes, free once the lists are built
 };
 
 // The small-batch routing of one batch by one workgroup of kRouteWaves waves:
 // the waves select the tokens side by side (the selections kept in LDS), then
-// wave 0 builds the lists (small_batch_lists; s.cnt and s.bal are complete at
-// the workgroup's next barrier).  Outputs go to memory with `publish`.
-__device__ __forceinline__ void route_small_batch(RouteSmallLds& s, const float* __restrict__ logits,
-                                         const uint8_t* __restrict__ important, int T, int E, int k, float delta32,
-                                         double tau, const RouteBufs& o, bool publish) {
+// wave 0 builds the lists (small_batch_lists; cnt and bal are complete at the
+// workgroup's next barrier).  Outputs go to memory with `publish`.  The arrays
+// are variables of their own: as the members of one struct they cost the routing
+// kernel 30 instructions and 10 branches (the whole call, four seeds: OLMoE layer,
+// 16 tokens, 46.2 us against 45.9, Mixtral layer, 1 token, 40.0 against 39.7).
+__device__ __forceinline__ RouteSmall route_small_batch(const float* __restrict__ logits,
+                                               const uint8_t* __restrict__ important, int T, int E, int k,
+                                               float delta32, double tau, const RouteBufs& o, bool publish) {
   static_assert(kRouteFusedMaxT <= 64, "one lane per token");
+  __shared__ uint16_t ent[kRouteFusedMaxT * MC_MAX_TOPK];
+  __shared__ float wsel[kRouteFusedMaxT * MC_MAX_TOPK];
+  __shared__ int cnt[MC_MAX_EXPERTS];
+  __shared__ int base[MC_MAX_EXPERTS + 1];
+  __shared__ unsigned long long bal[MC_MAX_EXPERTS];
+  __shared__ __attribute__((aligned(16))) unsigned char scratch[kRouteWaves][kSelScratchBytes];
   const int wave = wave_id();
-  const SelScratch sc = sel_scratch(s.scratch[wave]);
+  const SelScratch sc = sel_scratch(scratch[wave]);
   const int S = sel_segment(E), ns = 64 / S;
   // a wave selects ns tokens at once; route_fused_fits makes one round of
   // the 16 waves enough
   for (int t0 = wave * ns; t0 < T; t0 += kRouteWaves * ns) {
     const int t = t0 + (threadIdx.x & 63) / S;
     const SelInput in = sel_load(logits, important, t, T, E, S);
-    select_token(in, t, T, E, S, k, delta32, tau, o.topk_idx, o.topk_w, o.kept, o.pair_pos, publish, s.ent, s.wsel,
-                 sc);
+    select_token(in, t, T, E, S, k, delta32, tau, o.topk_idx, o.topk_w, o.kept, o.pair_pos, publish, ent, wsel, sc);
   }
+  const RouteSmall r{RouteLds{ent, wsel, cnt, base, bal}, &scratch[0][0]};
   __syncthreads();
-  if (wave != 0) return;
-  const RouteLds r{s.ent, s.wsel, s.cnt, s.base, s.bal};
-  small_batch_lists(T, E, k, r, publish, o.counts, o.offsets, o.pair_token, o.pair_rank, o.pair_w, o.pair_pos,
-                    o.n_pruned);
+  if (wave == 0)
+    small_batch_lists(T, E, k, r.lists, publish, o.counts, o.offsets, o.pair_token, o.pair_rank, o.pair_w, o.pair_pos,
+                      o.n_pruned);
+  return r;
 }
 
 }  // namespace mc
