@@ -67,7 +67,6 @@ struct DecodeArgs {
   int c_per;                  // chunks per split (the last split may be shorter)
   int gu_split;               // down: splits of the gate/up reduction (1: read h)
   int nwg;                    // workgroups in the grid
-  bool stream;                // weights by non-temporal loads (decode_streams)
 };
 
 // -------------------------------------------------------------- the plan --
@@ -113,6 +112,7 @@ __device__ __forceinline__ DecLane expert_lane(const LayerArgs& L, const DecodeA
 
 struct DecPiece {
   int e, b, s, C, u0, u1, pbase, nt;
+  int again;            // AUX only: the expert has more than one item, its words are read again
   uint32_t cb;
   uint32_t next;        // chunk position after the piece's item
   // set when the pieces are grouped (plan_round): pieces of one batch run
@@ -127,6 +127,7 @@ __device__ __forceinline__ int ceil_div_pos(int x, int y) { return x <= 0 ? 0 : 
 // x (lanes e0 + lane, whose items start at chunk position base): the item
 // containing pos and the row units of it whose first chunk lies in [lo, hi).
 // Returns false when pos is not in these experts.
+template <int AUX>
 __device__ __forceinline__ bool piece_in(const DecodeArgs& a, const DecLane& x, int e0, uint32_t base, int R,
                                          int ntiles, uint32_t lo, uint32_t hi, uint32_t pos, uint32_t incl,
                                          DecPiece& p) {
@@ -155,6 +156,7 @@ __device__ __forceinline__ bool piece_in(const DecodeArgs& a, const DecLane& x, 
   p.u1 = u1 < R ? u1 : R;
   p.s = s;
   p.C = C;
+  if constexpr (AUX != 0) p.again = ec > kDecTok;
   pair_block(eb, ec, j, kDecTok, p.pbase, p.nt);
   p.next = ib + (uint32_t)C * R;
   return true;
@@ -162,6 +164,7 @@ __device__ __forceinline__ bool piece_in(const DecodeArgs& a, const DecLane& x, 
 
 // The piece at pos, reading the routing counts again (pieces after the
 // first; they are rare: a share crosses at most a few items).
+template <int AUX>
 __device__ __forceinline__ DecPiece find_piece(const LayerArgs& L, const DecodeArgs& a, int R, int ntiles,
                                                uint32_t lo, uint32_t hi, uint32_t pos) {
   DecPiece p;
@@ -172,7 +175,7 @@ __device__ __forceinline__ DecPiece find_piece(const LayerArgs& L, const DecodeA
   for (int e0 = 0; e0 < L.E; e0 += 64) {
     const DecLane x = expert_lane(L, a, e0 + lane, (uint32_t)R * ntiles);
     const uint32_t incl = wave_incl_scan32(x.we);
-    if (piece_in(a, x, e0, base, R, ntiles, lo, hi, pos, incl, p)) return p;
+    if (piece_in<AUX>(a, x, e0, base, R, ntiles, lo, hi, pos, incl, p)) return p;
     base += __builtin_amdgcn_readlane(incl, 63);
   }
   return p;
@@ -517,6 +520,22 @@ __device__ __forceinline__ void decode_piece(const LayerArgs& L, const DecodeArg
     decode_run<BITS, GPC, F16, 1, AUX>(g, u0, u1, C, p.w0, p.w1, arow, sxs, tails, stage_early, stage_late, emit);
 }
 
+// Of a batch that streams past the memory-side cache (AUX), the words of an
+// expert with several items still go through it: every item after the first
+// finds them there (60 experts of 21.5 M weights, 64 tokens, Zipf routing: 103.1
+// us by ordinary loads, 106.1 all non-temporal, 99.7 so).
+template <int BITS, int GPC, bool GATEUP, int AUX>
+__device__ __forceinline__ void decode_piece_loads(const LayerArgs& L, const DecodeArgs& a, unsigned char* smem,
+                                                   const int32_t* s_tok, const DecPiece& p) {
+  if constexpr (AUX != 0) {
+    if (p.again) {
+      decode_piece<BITS, GPC, GATEUP, 0>(L, a, smem, s_tok, p);
+      return;
+    }
+  }
+  decode_piece<BITS, GPC, GATEUP, AUX>(L, a, smem, s_tok, p);
+}
+
 constexpr int kDecMaxPieces = 8;   // pieces planned per round (a share crosses few items)
 
 struct DecPlan {
@@ -550,7 +569,7 @@ __device__ __forceinline__ void share_waves(DecPlan& plan, int b0, int b1) {
 // Plans pieces from pos on (wave 0): up to kDecMaxPieces of them, the first
 // from the cached lanes x0 when pos == lo; then groups consecutive pieces
 // whose slabs fit the LDS together into batches.
-template <int GPC, int NW>
+template <int GPC, int NW, int AUX>
 __device__ __forceinline__ void plan_round(const LayerArgs& L, const DecodeArgs& a, const DecLane* x0,
                                            uint32_t incl0, int R, int ntiles, uint32_t lo, uint32_t hi,
                                            uint32_t pos, DecPlan& plan) {
@@ -558,8 +577,8 @@ __device__ __forceinline__ void plan_round(const LayerArgs& L, const DecodeArgs&
   int n = 0;
   while (pos < hi && n < kDecMaxPieces) {
     DecPiece p;
-    if (!(x0 && pos == lo && piece_in(a, *x0, 0, 0, R, ntiles, lo, hi, pos, incl0, p)))
-      p = find_piece(L, a, R, ntiles, lo, hi, pos);
+    if (!(x0 && pos == lo && piece_in<AUX>(a, *x0, 0, 0, R, ntiles, lo, hi, pos, incl0, p)))
+      p = find_piece<AUX>(L, a, R, ntiles, lo, hi, pos);
     pos = p.next > pos ? p.next : hi;    // always advances
     if (p.u0 >= p.u1) continue;
     if (lane == 0) plan.piece[n] = p;
@@ -620,7 +639,7 @@ decode_kernel(LayerArgs L, DecodeArgs a) {
     const uint32_t q = total / (uint32_t)a.nwg, rm = total % (uint32_t)a.nwg;
     lo = q * blockIdx.x + (rm * blockIdx.x) / a.nwg;
     hi = q * (blockIdx.x + 1) + (rm * (blockIdx.x + 1)) / a.nwg;
-    plan_round<GPC, NW>(L, a, &x0, incl0, R, ntiles, lo, hi, lo, plan);
+    plan_round<GPC, NW, AUX>(L, a, &x0, incl0, R, ntiles, lo, hi, lo, plan);
   } else if (GATEUP) {
     for (int i = (wave - 1) * 64 + lane; i < a.P; i += (NW - 1) * 64) s_tok[i] = a.pair_token[i];
   }
@@ -635,15 +654,15 @@ decode_kernel(LayerArgs L, DecodeArgs a) {
         if (plan.piece[i].batch == bt && plan.piece[i].w0 <= wave && wave < plan.piece[i].w1) mine = i;
       const DecPiece p = plan.piece[mine];
       if (p.b == 1)
-        decode_piece<1, GPC, GATEUP, AUX>(L, a, smem, s_tok, p);
+        decode_piece_loads<1, GPC, GATEUP, AUX>(L, a, smem, s_tok, p);
       else if (p.b == 2)
-        decode_piece<2, GPC, GATEUP, AUX>(L, a, smem, s_tok, p);
+        decode_piece_loads<2, GPC, GATEUP, AUX>(L, a, smem, s_tok, p);
       else
-        decode_piece<3, GPC, GATEUP, AUX>(L, a, smem, s_tok, p);
+        decode_piece_loads<3, GPC, GATEUP, AUX>(L, a, smem, s_tok, p);
     }
     if (!more) break;
     __syncthreads();                 // every wave has read the plan and left the slab
-    if (wave == 0) plan_round<GPC, NW>(L, a, nullptr, 0, R, ntiles, lo, hi, plan.pos, plan);
+    if (wave == 0) plan_round<GPC, NW, AUX>(L, a, nullptr, 0, R, ntiles, lo, hi, plan.pos, plan);
     __syncthreads();
   }
 }
@@ -657,14 +676,17 @@ decode_kernel(LayerArgs L, DecodeArgs a) {
 inline int decode_waves(bool gateup, int T) { return T <= (gateup ? 8 : 4) ? 8 : 16; }
 
 // Whether a batch's weights are read by non-temporal loads, which leave the
-// memory-side cache (256 MB) to other data.  Where a call touches more than
-// that cache keeps, allocating its stream there only costs: Mixtral layer
-// (485 MB), 8 tokens: 112 -> 98 us a call, 16: 115 -> 101, 32: 118 -> 106 (the
-// same with three layers rotated).  Where it touches less, the next call may
-// find it there: Mixtral layer at 4 tokens (331 MB) 58.5 -> 59.8 us repeated,
-// 61.6 -> 59.8 rotated; 8 experts of 11 M weights, 1 token 23.9 -> 25.5; 60 of
-// 21.5 M, 4 tokens 53.8 -> 63.5.  Bytes of the experts
-// an even routing touches, against one and a half times the cache.
+// memory-side cache (256 MB) to other data (decode_piece_loads: but for experts
+// read more than once).  Where a call touches more than that cache keeps,
+// allocating its stream there only costs: Mixtral layer (485 MB), the whole call,
+// layers in turn, mean of even, biased and Zipf routing with and without pruning:
+// 8 tokens 98.7 -> 91.5 us, 16: 115.2 -> 105.5, 32: 127.0 -> 119.4, 48: 151.2 ->
+// 147.2; 64 experts of 25 M weights, 16 tokens 106.8 -> 100.6, 64: 149.3 -> 143.4.
+// Where it touches less, the next call may find it there: Mixtral layer at 4
+// tokens (331 MB) 58.5 -> 59.8 us repeated, 61.6 -> 59.8 layers in turn; 8 experts
+// of 11 M weights, 1 token 23.9 -> 25.5; 60 of 21.5 M, 4 tokens 53.8 -> 63.5.
+// Bytes of the experts an even routing touches, against one and a half times the
+// cache.
 inline bool decode_streams(const LayerArgs& L, int T, int k) {
   const double touched = 1.0 - pow(1.0 - (double)k / L.E, (double)T);
   const double bytes = 3.0 * L.d * L.ffn * (L.cum_bits[L.E] / 8.0 + 4.0 * L.E / L.G);
@@ -683,13 +705,14 @@ hipError_t launch_decode_nw(const LayerArgs& L, const DecodeArgs& a, hipStream_t
   return hipGetLastError();
 }
 
+// streams: decode_streams.
 template <int GPC, bool GATEUP>
-hipError_t launch_decode(const LayerArgs& L, const DecodeArgs& a, hipStream_t stream) {
+hipError_t launch_decode(const LayerArgs& L, const DecodeArgs& a, bool streams, hipStream_t stream) {
   if (decode_waves(GATEUP, a.T) == 8)
-    return a.stream ? launch_decode_nw<GPC, GATEUP, 8, kNonTemporal>(L, a, stream)
-                    : launch_decode_nw<GPC, GATEUP, 8, 0>(L, a, stream);
-  return a.stream ? launch_decode_nw<GPC, GATEUP, 16, kNonTemporal>(L, a, stream)
-                  : launch_decode_nw<GPC, GATEUP, 16, 0>(L, a, stream);
+    return streams ? launch_decode_nw<GPC, GATEUP, 8, kNonTemporal>(L, a, stream)
+                   : launch_decode_nw<GPC, GATEUP, 8, 0>(L, a, stream);
+  return streams ? launch_decode_nw<GPC, GATEUP, 16, kNonTemporal>(L, a, stream)
+                 : launch_decode_nw<GPC, GATEUP, 16, 0>(L, a, stream);
 }
 
 }  // namespace mc

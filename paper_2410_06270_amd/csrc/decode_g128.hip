@@ -2,6 +2,6 @@
 #include "decode.hpp"
 
 namespace mc {
-template hipError_t launch_decode<1, true>(const LayerArgs&, const DecodeArgs&, hipStream_t);
-template hipError_t launch_decode<1, false>(const LayerArgs&, const DecodeArgs&, hipStream_t);
+template hipError_t launch_decode<1, true>(const LayerArgs&, const DecodeArgs&, bool, hipStream_t);
+template hipError_t launch_decode<1, false>(const LayerArgs&, const DecodeArgs&, bool, hipStream_t);
 }  // namespace mc

@@ -6,6 +6,13 @@
 
 namespace mc {
 
+extern template hipError_t launch_decode<1, true>(const LayerArgs&, const DecodeArgs&, bool, hipStream_t);
+extern template hipError_t launch_decode<1, false>(const LayerArgs&, const DecodeArgs&, bool, hipStream_t);
+extern template hipError_t launch_decode<2, true>(const LayerArgs&, const DecodeArgs&, bool, hipStream_t);
+extern template hipError_t launch_decode<2, false>(const LayerArgs&, const DecodeArgs&, bool, hipStream_t);
+extern template hipError_t launch_decode<4, true>(const LayerArgs&, const DecodeArgs&, bool, hipStream_t);
+extern template hipError_t launch_decode<4, false>(const LayerArgs&, const DecodeArgs&, bool, hipStream_t);
+
 // ---------------------------------------------------------------- combine --
 // y[t][i..i+3] = bf16(res[t][i..i+3] + sum over kept ranks r, in rank order,
 // of w_r * sum over splits s, in order, of partial[s][pos(t, r)][i..i+3]);
@@ -349,7 +356,7 @@ hipError_t launch_expert_partials(const uint16_t* x, const LayerArgs& L, const m
   a.T = T;
   a.P = (int)P;
   a.nwg = device_cus();
-  a.stream = decode_streams(L, T, k);
+  const bool streams = decode_streams(L, T, k);
   int c_gu = 0, c_dn = 0;
   const int s_gu = decode_splits(L.d, &c_gu);
   const int nsplit = decode_splits(L.ffn, &c_dn);
@@ -374,9 +381,9 @@ hipError_t launch_expert_partials(const uint16_t* x, const LayerArgs& L, const m
   a.gu_split = 1;
   hipError_t err;
   timing_begin(stream, kSiteGateUp);
-  if (L.G == 128) err = launch_decode<1, true>(L, a, stream);
-  else if (L.G == 64) err = launch_decode<2, true>(L, a, stream);
-  else err = launch_decode<4, true>(L, a, stream);
+  if (L.G == 128) err = launch_decode<1, true>(L, a, streams, stream);
+  else if (L.G == 64) err = launch_decode<2, true>(L, a, streams, stream);
+  else err = launch_decode<4, true>(L, a, streams, stream);
   timing_end(stream, kSiteGateUp);
   if (err != hipSuccess) return err;
 
@@ -390,9 +397,9 @@ hipError_t launch_expert_partials(const uint16_t* x, const LayerArgs& L, const m
   a.c_per = c_dn;
   a.gu_split = s_gu;
   timing_begin(stream, kSiteDown);
-  if (L.G == 128) err = launch_decode<1, false>(L, a, stream);
-  else if (L.G == 64) err = launch_decode<2, false>(L, a, stream);
-  else err = launch_decode<4, false>(L, a, stream);
+  if (L.G == 128) err = launch_decode<1, false>(L, a, streams, stream);
+  else if (L.G == 64) err = launch_decode<2, false>(L, a, streams, stream);
+  else err = launch_decode<4, false>(L, a, streams, stream);
   timing_end(stream, kSiteDown);
   return err;
 }
