@@ -199,21 +199,32 @@ static int decode_splits(int K, int* c_per) {
 // prefill path).  Up to kDecodeMaxT tokens the GEMVs stream the weights
 // faster, but once per 16 pairs of an expert, and every piece of a matrix
 // costs a workgroup a set-up; the GEMMs stream them once per 32 pairs and pay
-// one more launch, which routes too with up to 16 experts.  So the GEMMs take
-// batches with 12 or more pairs an expert (Mixtral layer at 32 tokens: GEMVs 124
-// us, GEMMs 136; 48: 143 and 146; 64: 167 and 151), and from 12 tokens on the
-// layers whose touched experts are small: with up to 16 experts up to 250 M
-// weights (even routing, 16 tokens: 16 experts of 12.6 M 38.3 and 35.6 us; of 25
-// M 47.2 and 53.7, skewed 37.9 and 38.1; 8 of 44 M 55.0 and 58.6), with more,
-// whose many half-empty m-tiles cost the GEMMs most where the routing is even,
-// up to 60 M (60 of 0.8 M: 31.8 and 30.6; 24 of 4.9 M: 34.2 and 35.5; OLMoE layer,
-// 64 of 6.3 M: 56.8 and 64.1, skewed 47.2 and 44.4; at 32 tokens 54.9 and 68.3,
-// 54.3 and 56.0).  A small batch whose GEMM workspace would not fit the
-// library's own scratch keeps the GEMVs.
+// one more launch, which routes too with up to 16 experts.  How often an expert
+// has more than 16 pairs depends on the routing, which is not known here: the
+// lines lie where the means over even, biased and Zipf routing, with and without
+// pruning, meet (us a call, GEMVs and GEMMs, layers in turn).
+//   Pairs an expert: layers that the GEMVs read by non-temporal loads (about 1.1 G
+// weights on, see decode_streams) take the GEMMs from 14 on: Mixtral layer at
+// 12 pairs (48 tokens) 147.2 and 147.5, 13: 152.2 and 150.3, 14: 157.2 and 149.6,
+// 16: 169.5 and 151.9; 16 experts of 4096 x 8192, top-4, at 12: 159.7 and 167.5, 14:
+// 176.2 and 168.7.  (Between 12 and 14 Mixtral's mean is up to 4 % lower on the
+// GEMMs, but an even routing's calls take 8 to 14 % longer there.)  The others
+// from 12 on: 4 experts of 4096 x 14336 at 10: 81.9 and 86.0, 12: 88.3 and 86.7,
+// 14: 100.6 and 87.1; 16 of 2048 x 8192 at 8: 90.5 and 95.4, 10: 98.0 and 97.4, 12:
+// 104.9 and 99.5.
+//   Touched weights: from 12 tokens on the GEMMs take small layers, with up to 16
+// experts up to 250 M weights (8 of 25 M, 12 tokens 41.8 and 38.1; 16 of 12.6 M
+// 37.9 and 35.9; 8 of 44 M 53.3 and 55.1).  With more experts the routing has its
+// own launch, and many half-empty m-tiles cost the GEMMs most where the routing
+// is even: up to 60 M (20 of 3.1 M, 16 tokens 31.6 and 30.7; 24 of 4.9 M 34.2 and
+// 35.5; 17 of 12.6 M 39.9 and 40.4; OLMoE layer, 64 of 6.3 M, 52.5 and 58.4).
+//   A small batch whose GEMM workspace would not fit the library's own scratch
+// keeps the GEMVs.
 static bool gemms_pay(int T, int E, int k, int d, int ffn) {
   if (T > kDecodeMaxT) return true;
-  const double touched = (double)(T * k < E ? T * k : E) * 3.0 * d * ffn;
-  return (double)T * k >= 12.0 * E || (T >= 12 && touched <= (E <= 16 ? 250e6 : 60e6));
+  const double expert = 3.0 * d * ffn;
+  if ((double)T * k >= (E * expert >= 1.1e9 ? 14.0 : 12.0) * E) return true;
+  return T >= 12 && (T * k < E ? T * k : E) * expert <= (E <= 16 ? 250e6 : 60e6);
 }
 
 static bool use_decode(int T, int E, int k, int d, int ffn) {

@@ -99,6 +99,7 @@ def forward(mc, L, r, x, T, k):
     (STREAMED, 8, 4, 4, None),            # 16-wave ones for down
     (STREAMED, 17, 2, 17, (17, 17)),
     (STREAMED, 47, 2, 33, (47, 33)),
+    (STREAMED, 52, 2, 20, (52, 20)),      # streamed layers keep the GEMVs up to 14 pairs an expert
     (SPLIT, 17, 2, 17, (17, 17)),
 ])
 @pytest.mark.parametrize("G", [32, 64, 128])
