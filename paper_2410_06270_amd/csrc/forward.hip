@@ -212,19 +212,23 @@ static int decode_splits(int K, int* c_per) {
 // from 12 on: 4 experts of 4096 x 14336 at 10: 81.9 and 86.0, 12: 88.3 and 86.7,
 // 14: 100.6 and 87.1; 16 of 2048 x 8192 at 8: 90.5 and 95.4, 10: 98.0 and 97.4, 12:
 // 104.9 and 99.5.
-//   Touched weights: from 12 tokens on the GEMMs take small layers, with up to 16
-// experts up to 250 M weights (8 of 25 M, 12 tokens 41.8 and 38.1; 16 of 12.6 M
-// 37.9 and 35.9; 8 of 44 M 53.3 and 55.1).  With more experts the routing has its
-// own launch, and many half-empty m-tiles cost the GEMMs most where the routing
-// is even: up to 60 M (20 of 3.1 M, 16 tokens 31.6 and 30.7; 24 of 4.9 M 34.2 and
-// 35.5; 17 of 12.6 M 39.9 and 40.4; OLMoE layer, 64 of 6.3 M, 52.5 and 58.4).
+//   Touched weights: the GEMMs take small layers, with up to 16 experts up to 110
+// M weights from 12 tokens and 250 M from 16 (8 of 11 M, 12 tokens 35.7 and 30.7;
+// of 25 M, 16 tokens 43.2 and 38.4; 16 of 12.6 M 39.9 and 37.2; 8 of 44 M 56.2 and
+// 56.3).  Where the routing is apart, as in a stack, the GEMMs' preparation is one
+// more launch: a layer of 8 of 11 M, 12 tokens 32.8 and 31.5, of 25 M 38.6 and 39.3,
+// 16 tokens 40.5 and 39.5; 16 of 12.6 M, 12 tokens 35.1 and 36.7, 16: 36.2 and 36.9, 24:
+// 38.2 and 38.1.  With more experts it always is, and many half-empty m-tiles cost
+// the GEMMs most where the routing is even: up to 60 M (20 of 3.1 M, 16 tokens 31.6
+// and 30.7; 24 of 4.9 M 34.2 and 35.5; 17 of 12.6 M 39.9 and 40.4; OLMoE layer, 64 of
+// 6.3 M, 52.5 and 58.4).
 //   A small batch whose GEMM workspace would not fit the library's own scratch
 // keeps the GEMVs.
 static bool gemms_pay(int T, int E, int k, int d, int ffn) {
   if (T > kDecodeMaxT) return true;
   const double expert = 3.0 * d * ffn;
   if ((double)T * k >= (E * expert >= 1.1e9 ? 14.0 : 12.0) * E) return true;
-  return T >= 12 && (T * k < E ? T * k : E) * expert <= (E <= 16 ? 250e6 : 60e6);
+  return T >= 12 && (T * k < E ? T * k : E) * expert <= (E > 16 ? 60e6 : T < 16 ? 110e6 : 250e6);
 }
 
 static bool use_decode(int T, int E, int k, int d, int ffn) {

@@ -23,7 +23,7 @@ SPLIT = (4, 4608, 8192)
 
 @pytest.fixture(scope="module")
 def layer():
-    """layer(shape, G) -> the packed layer, made once."""
+    """layer(shape, G) -> the packed layer, made once in a row."""
     import paper_2410_06270_amd as mc
     made = {}
 
@@ -33,7 +33,7 @@ def layer():
             torch.cuda.empty_cache()
             E, d, ffn = shape
             g = torch.Generator(device="cuda").manual_seed(d + G)
-            L = mc.PackedLayer(E, d, ffn, BITS[:E], G)
+            L = mc.PackedLayer(E, d, ffn, [BITS[e % len(BITS)] for e in range(E)], G)
             mc.pack(*(torch.randn(s, generator=g, device="cuda").mul_(0.02)
                       for s in ((E, ffn, d), (E, ffn, d), (E, d, ffn))), L)
             torch.cuda.synchronize()
@@ -77,15 +77,17 @@ def skewed_logits(T, E, k, second, g):
     return lg
 
 
-def forward(mc, L, r, x, T, k):
-    """mc_moe_forward on a batch that must take the GEMVs; NaN where not written."""
+def forward(mc, L, r, x, T, k, gemvs=True):
+    """mc_moe_forward on a batch that must take the GEMVs (or the GEMMs); NaN
+    where not written."""
     y = torch.full((T, L.d), 0x7FC1, dtype=torch.int16, device="cuda")
     ws = torch.empty(mc.forward_workspace(T, L.E, k, L.d, L.ffn), dtype=torch.uint8, device="cuda")
     mc.timing_enable(True)
     try:
         mc.moe_forward(x.view(torch.int16), r, L, y, ws)
         torch.cuda.synchronize()
-        assert mc.timing_read("prefill_prep")[1] == 0 and mc.timing_read("gateup")[1] == 1
+        assert mc.timing_read("gateup")[1] == 1
+        assert mc.timing_read("prefill_prep")[1] == (0 if gemvs else 1)
     finally:
         mc.timing_enable(False)
     return y
@@ -123,6 +125,30 @@ def test_gemv_blocks(layer, G, shape, T, k, second, counts):
     # outputs are several times a 3-bit one's) and eight of them stay below 2^-9
     rms = want.square().mean(dim=1, keepdim=True).sqrt()
     assert ((got - want).abs() <= 2.0 ** -8 * want.abs() + 2.0 ** -9 * rms).all()
+
+
+@pytest.mark.parametrize("shape,T", [
+    (ORDINARY, 47),                # 12 pairs an expert
+    (STREAMED, 55),                # 14
+    ((8, 1024, 3584), 11),         # up to 110 M weights: 12 tokens
+    ((16, 2048, 2048), 15),        # up to 250 M: 16 tokens
+    ((20, 512, 1024), 11),         # more than 16 experts, up to 60 M: 12 tokens
+])
+def test_last_gemv_batch(layer, shape, T):
+    """Where the GEMVs hand over to the GEMMs: T tokens take the former, T + 1
+    the latter, and both agree on the tokens they share."""
+    import paper_2410_06270_amd as mc
+    L = layer(shape, 128)
+    x = torch.randn((T + 1, L.d), generator=torch.Generator(device="cuda").manual_seed(T), device="cuda").to(torch.bfloat16)
+    lg = torch.randn((T + 1, L.E), generator=torch.Generator(device="cuda").manual_seed(T + 1), device="cuda")
+    y = []
+    for n in (T, T + 1):
+        r = mc.Routing(n, L.E, 2)
+        mc.route_and_prune(lg[:n], None, 0.3, r)
+        y.append(forward(mc, L, r, x[:n], n, 2, gemvs=n == T).view(torch.bfloat16)[:T].double())
+    # one bf16 rounding and the rounding of h on each side (see test_gemv_blocks)
+    rms = y[1].square().mean(dim=1, keepdim=True).sqrt()
+    assert ((y[0] - y[1]).abs() <= 2.0 ** -7 * y[1].abs() + 2.0 ** -8 * rms).all()
 
 
 @pytest.mark.parametrize("shape", [ORDINARY, STREAMED])
