@@ -531,10 +531,10 @@ prefill_kernel(LayerArgs L, const int32_t* __restrict__ offsets, PrefillTables t
     // (numbered t * 16 + i: the gate wave forms the first half, the up wave
     // the second) through LDS, and forms h = silu(gate) * up rounded to fp16
     // for its own half, into an LDS copy of the workgroup's h tile laid out as
-    // in global memory (per fragment row 8 KB: its 128 columns are 8
-    // consecutive 1 KB fragments); all threads then store the tile with
-    // 16-byte writes, and the group sums of the rounded h are read back from
-    // it, each in column order.
+    // in global memory (per fragment row its kRowsGateUp columns, consecutive
+    // 1 KB fragments of 16); all threads then store the tile with 16-byte
+    // writes, and the group sums of the rounded h are read back from it, each in
+    // column order.
     __syncthreads();                       // the ring is free
     constexpr int HO = S::kHandOver;
     constexpr int HT = S::kRowsGateUp / 16 * kPfFragBytes;                     // bytes of a fragment row of the tile
@@ -549,16 +549,21 @@ prefill_kernel(LayerArgs L, const int32_t* __restrict__ offsets, PrefillTables t
       const int c = 32 * rb + n;           // column within the workgroup's
       const int partner = wave ^ 1;
 #pragma unroll
-      for (int v = 0; v < HO; ++v) {
-        const int id = upw ? v + HO : v;   // the total this wave forms: fragment row id / 16
-        if (id >> 4 >= nmt) continue;
-        const int i = id & 15;
-        const int m = 8 * (i >> 2) + 4 * (lane >> 5) + (i & 3);
-        const float other = xch[(partner * HO + v) * 64 + lane];
-        const float mine = upw ? tot[(v + HO) >> 4][(v + HO) & 15] : tot[v >> 4][v & 15];
-        const float gv = upw ? other : mine, uv = upw ? mine : other;
-        *reinterpret_cast<uint16_t*>(ht + (size_t)(id >> 4) * HT + frag_offset(0, m, c, S::kRowsGateUp)) =
-            float_to_half_sat(silu(gv) * uv);
+      for (int v0 = 0; v0 < HO; v0 += 16) {
+        // totals v0 .. v0 + 15 of this wave's half, all of one fragment row, which is
+        // checked once (for every total: Mixtral layer, 4096 tokens, 2.90 -> 2.93 ms)
+        const int id0 = upw ? v0 + HO : v0, t = id0 >> 4;
+        if (t >= nmt) continue;
+#pragma unroll
+        for (int v = v0; v < v0 + (HO < 16 ? HO : 16); ++v) {
+          const int i = (upw ? v + HO : v) & 15;
+          const int m = 8 * (i >> 2) + 4 * (lane >> 5) + (i & 3);
+          const float other = xch[(partner * HO + v) * 64 + lane];
+          const float mine = upw ? tot[(v + HO) >> 4][(v + HO) & 15] : tot[v >> 4][v & 15];
+          const float gv = upw ? other : mine, uv = upw ? mine : other;
+          *reinterpret_cast<uint16_t*>(ht + (size_t)t * HT + frag_offset(0, m, c, S::kRowsGateUp)) =
+              float_to_half_sat(silu(gv) * uv);
+        }
       }
     }
     __syncthreads();
