@@ -15,22 +15,22 @@ extern template hipError_t launch_prefill_gemm<2>(const LayerArgs&, const int32_
 extern template hipError_t launch_prefill_gemm<4>(const LayerArgs&, const int32_t*, const PrefillTables&,
                                                   const PrefillGemm&, bool, int, hipStream_t);
 
-// The prefill's preparation, one workgroup per fragment row f (f_max of
-// them).  Every workgroup first scans the expert counts itself (thread e:
-// fragment rows ceil(M_e/32) and m-tiles of tb.tiles fragment rows; wave
-// prefix sums), which gives the expert that f belongs to; workgroup 0 also
-// writes the tables the GEMMs read.  Counts outside [0, P] are taken as 0,
-// and tables that would not fit their capacity are left empty (no m-tiles,
-// no fragment rows), so inconsistent routing cannot make any later access
-// leave its buffer.
-// Then f's 32 routed rows of x (zero past the expert's count) are copied
-// into the fragment layout (bf16, unchanged), with the sum of each group of G
-// columns of each row in fp32.  Column blocks of 512:
-// each wave reads whole rows of the block (64 lanes x 16 consecutive bytes)
-// into a row-major LDS tile and forms the group sums of its pieces (the GP =
-// G/8 lanes of a group add with the DPP butterfly of the decode slabs); then
-// the workgroup writes the block's fragments (contiguous in the fragment
-// layout) from the tile with consecutive 16-byte stores.
+// The prefill's preparation, one workgroup per fragment row f (f_max of them)
+// and block of kGatherCols columns.  Every workgroup first scans the expert
+// counts itself (thread e: fragment rows ceil(M_e/32) and m-tiles of tb.tiles
+// fragment rows; wave prefix sums), which gives the expert that f belongs to;
+// the first one also writes the tables the GEMMs read.  Counts outside [0, P]
+// are taken as 0, and tables that would not fit their capacity are left empty
+// (no m-tiles, no fragment rows), so inconsistent routing cannot make any later
+// access leave its buffer.
+// Then the block of f's 32 routed rows of x (zero past the expert's count) is
+// copied into the fragment layout (bf16, unchanged), with the sum of each group
+// of G columns of each row in fp32: each wave reads whole rows of the block (64
+// lanes x 16 consecutive bytes) into a row-major LDS tile and forms the group
+// sums of its pieces (the GP = G/8 lanes of a group add with the DPP butterfly of
+// the decode slabs); then the workgroup writes the block's fragments
+// (contiguous in the fragment layout) from the tile with consecutive 16-byte
+// stores.
 constexpr int kGatherThreads = 256;
 constexpr int kGatherCols = 512;                     // columns of a block: 8 per lane
 constexpr int kGatherStride = kGatherCols + 8;       // LDS row stride (elements): rows start on different banks
@@ -107,40 +107,42 @@ __global__ void __launch_bounds__(kGatherThreads) prefill_prep_kernel(const uint
   const int pos0 = ebase + (f - s_fb) * kPfFragRows;
   const int pend = ebase + ecount;
   constexpr int kRowsPerWave = kPfFragRows / (kGatherThreads / 64);
-  // this wave's rows: m = wave + 4 j; token rows (or none: zero rows)
+  // this wave's rows: m = wave + 4 j; their token rows of x (past the list: row 0,
+  // read and dropped, so that every load goes out before the first use; behind
+  // branches each waited for the one before it: Mixtral layer, 4096 tokens, 26 us
+  // -> 47)
   const uint16_t* src[kRowsPerWave];
 #pragma unroll
   for (int j = 0; j < kRowsPerWave; ++j) {
     const int pos = pos0 + wave + 4 * j;
-    src[j] = pos < pend ? x + (size_t)clamp_token(pair_token[pos], tb.T) * d : nullptr;
+    src[j] = x + (size_t)(pos < pend ? clamp_token(pair_token[pos], tb.T) : 0) * d;
   }
   const int ng = d / (8 * GP);
   unsigned char* out = reinterpret_cast<unsigned char*>(xt) + frag_offset(f, 0, 0, d);
-  for (int c0 = blockIdx.y * kGatherCols; c0 < d; c0 += gridDim.y * kGatherCols) {
-    const int w = (d - c0) < kGatherCols ? (d - c0) : kGatherCols;   // a multiple of 128
-    const bool on = 8 * lane < w;
-    u32x4 v[kRowsPerWave];
+  const int c0 = blockIdx.y * kGatherCols;
+  const int w = (d - c0) < kGatherCols ? (d - c0) : kGatherCols;   // a multiple of 128
+  const bool on = 8 * lane < w;
+  u32x4 v[kRowsPerWave];
 #pragma unroll
-    for (int j = 0; j < kRowsPerWave; ++j) {
-      v[j] = u32x4{0u, 0u, 0u, 0u};
-      if (on && src[j]) v[j] = *reinterpret_cast<const u32x4*>(src[j] + c0 + 8 * lane);
-    }
-    if (c0 >= (int)gridDim.y * kGatherCols) __syncthreads();   // the previous block's tile has been written out
+  for (int j = 0; j < kRowsPerWave; ++j)
+    v[j] = *reinterpret_cast<const u32x4*>(src[j] + c0 + (on ? 8 * lane : 0));
 #pragma unroll
-    for (int j = 0; j < kRowsPerWave; ++j) {
-      const int m = wave + 4 * j;
-      if (on) *reinterpret_cast<u32x4*>(tile + m * kGatherStride + 8 * lane) = v[j];
-      const float sum = lane_group_sum<GP>(sum8<false>(v[j]));
-      if (on && lane % GP == 0) xsum[((size_t)f * ng + (c0 + 8 * lane) / (8 * GP)) * 32 + m] = sum;
-    }
-    __syncthreads();
-    // fragment fi of the block, piece mm: row mm % 32, columns 16 fi + 8 (mm / 32)
-    const int pieces = (w / 16) * 64;
-    for (int p = threadIdx.x; p < pieces; p += kGatherThreads) {
-      const int fi = p >> 6, mm = p & 63;
-      *reinterpret_cast<u32x4*>(out + ((size_t)(c0 / 16 + fi) * 64 + mm) * 16) =
-          *reinterpret_cast<const u32x4*>(tile + (mm & 31) * kGatherStride + 16 * fi + 8 * (mm >> 5));
-    }
+  for (int j = 0; j < kRowsPerWave; ++j)
+    if (pos0 + wave + 4 * j >= pend) v[j] = u32x4{0u, 0u, 0u, 0u};
+#pragma unroll
+  for (int j = 0; j < kRowsPerWave; ++j) {
+    const int m = wave + 4 * j;
+    if (on) *reinterpret_cast<u32x4*>(tile + m * kGatherStride + 8 * lane) = v[j];
+    const float sum = lane_group_sum<GP>(sum8<false>(v[j]));
+    if (on && lane % GP == 0) xsum[((size_t)f * ng + (c0 + 8 * lane) / (8 * GP)) * 32 + m] = sum;
+  }
+  __syncthreads();
+  // fragment fi of the block, piece mm: row mm % 32, columns 16 fi + 8 (mm / 32)
+  const int pieces = (w / 16) * 64;
+  for (int p = threadIdx.x; p < pieces; p += kGatherThreads) {
+    const int fi = p >> 6, mm = p & 63;
+    *reinterpret_cast<u32x4*>(out + ((size_t)(c0 / 16 + fi) * 64 + mm) * 16) =
+        *reinterpret_cast<const u32x4*>(tile + (mm & 31) * kGatherStride + 16 * fi + 8 * (mm >> 5));
   }
 }
 
