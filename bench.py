@@ -455,9 +455,10 @@ def gptq_entry(mc, torch, synthetic):
     """GPTQ (fp64) of one Mixtral expert's gate matrix (14336 x 4096, 3 bits)
     and down matrix (4096 x 14336, 2 bits), G = 128, from 8192 calibration
     rows each, timed per stage with the library's HIP events (one run after
-    a warm-up run).  Work per stage: Hessian 2*N*K^2 flops; factor (Cholesky
-    and triangular inverse) 4/3*K^3; quantize R*K^2 (one multiply and one
-    subtract per compensation term).  Peak: 78.6 fp64 TFLOP/s."""
+    a warm-up run).  Work per stage: Hessian N*K*(K+64) flops (the 64 x 64 tiles
+    of the lower triangle); factor (Cholesky and triangular inverse) 4/3*K^3;
+    quantize R*K^2 (one multiply and one subtract per compensation term).  Peak:
+    78.6 fp64 TFLOP/s."""
     FP64_PEAK_TFLOPS = 78.6
     runs = []
     for name, (R, K, bits, tag) in (("gate", (14336, 4096, 3, 1)), ("down", (4096, 14336, 2, 2))):
@@ -485,7 +486,7 @@ def gptq_entry(mc, torch, synthetic):
             t, _ = mc.timing_read(st)
             ms[st] = t
         mc.timing_enable(False)
-        flops = {"gptq_hessian": 2.0 * N * K * K, "gptq_factor": 4.0 / 3.0 * K ** 3, "gptq_quantize": 1.0 * R * K * K}
+        flops = {"gptq_hessian": 1.0 * N * K * (K + 64), "gptq_factor": 4.0 / 3.0 * K ** 3, "gptq_quantize": 1.0 * R * K * K}
         runs.append(dict(matrix=name, rows=R, inputs=K, bits=bits, calib_rows=N,
                          ms={k: round(v, 2) for k, v in ms.items()},
                          fp64_tflops={k: round(flops[k] / (ms[k] * 1e-3) / 1e12, 2) for k in ms},
@@ -554,6 +555,11 @@ def stack_entry(mc, torch, synthetic, steps, warmup, graph=True):
         ev1.record()
         torch.cuda.synchronize()
         ms = ev0.elapsed_time(ev1) / steps
+        mc.timing_enable(True)                  # which expert kernels the layers took
+        run()
+        torch.cuda.synchronize()
+        path = "gemm" if mc.timing_read("prefill_prep")[1] else "gemv"
+        mc.timing_enable(False)
         ms_graph = None
         if graph and T <= 64:
             gr = torch.cuda.CUDAGraph()
@@ -570,7 +576,7 @@ def stack_entry(mc, torch, synthetic, steps, warmup, graph=True):
             ms_graph = ev0.elapsed_time(ev1) / steps
             del gr
         flops = 6 * d * ffn * kept
-        runs.append(dict(tokens=T, path="decode" if T <= 64 else "prefill", ms_per_step=round(ms, 4),
+        runs.append(dict(tokens=T, path=path, ms_per_step=round(ms, 4),
                          ms_per_step_graph=ms_graph and round(ms_graph, 4),
                          tokens_per_s_graph=ms_graph and round(T / (ms_graph / 1e3), 1),
                          tokens_per_s=round(T / (ms / 1e3), 1),
@@ -590,8 +596,8 @@ def main():
     args = parse()
     world = int(os.environ.get("WORLD_SIZE", "1"))
     if args.gpus > 1 or world > 1:
-        print("bench.py measures one GPU only: this build has no multi-GPU path "
-              "(the sharding design is described in DESIGN.md); run with --gpus 1",
+        print("bench.py measures one GPU only: there is no multi-GPU path"
+              "; run with --gpus 1",
               file=sys.stderr)
         sys.exit(2)
     import torch

@@ -382,10 +382,12 @@ mc_status mc_pmq_expert_error(const float *w_gate, const float *w_up, const floa
  * mc_timing_enable(0) stops recording.  mc_timing_read waits for the recorded
  * events of one kernel and returns the summed duration in ms and the number
  * of launches.  Kernel names: pack_scale_zero (the l1 scales of sign-binarized
- * experts), pack_codes (codes and scale/zero words), export,
- * route_fused, route_select, route_lists, prefill_prep, gateup, down, combine,
- * importance_colsum, importance_finish, importance_select, rmsnorm, router,
- * gptq_hessian, gptq_factor, gptq_quantize (each a whole call).
+ * experts), pack_codes (codes and scale/zero words), export, route_fused (the
+ * routing of a small batch in one launch; where it shares a launch with the
+ * GEMMs' preparation, that launch, and none as prefill_prep), route_select,
+ * route_lists, prefill_prep, gateup, down, combine, importance_colsum,
+ * importance_finish, importance_select, rmsnorm, router, gptq_hessian,
+ * gptq_factor, gptq_quantize (each a whole call).
  * Errors: MC_EINVAL (unknown name, NULL pointer), MC_EHIP. */
 mc_status mc_timing_enable(int on);
 mc_status mc_timing_read(const char *kernel, double *total_ms, int *launches);

@@ -22,8 +22,8 @@
 // mirrored), the Cholesky trailing updates and the inverse's corner blocks;
 // GPTQ's deferred updates run one column after the other with every product
 // and subtraction rounded, which no MFMA does, on a register-tiled fp64 kernel;
-// the sequential parts are one workgroup (64 x 64 Cholesky), a lane per row
-// (panel solve) and four lanes per row (the GPTQ column loop).
+// the sequential parts are one workgroup (64 x 64 Cholesky) and four lanes per
+// row (panel solve, GPTQ column loop).
 #include <type_traits>
 
 #include "mc_internal.hpp"

@@ -4,8 +4,8 @@ the benchmark times.  Packed words are compared in full for one expert; the
 layer output is compared on sampled tokens x rows, which the oracle computes
 one by one from its own quantization of the same fp32 weights: every token
 and row for decode batches, and for prefill one token from every 64 routed
-pairs of every expert (two per 128-token m-tile of the grouped GEMMs) over
-rows covering every 256-row tile of the down GEMM."""
+pairs of every expert (one per 64-token m-tile of the grouped GEMMs, two per
+128-token one) over rows covering every 256-row tile of the down GEMM."""
 import numpy as np
 import pytest
 

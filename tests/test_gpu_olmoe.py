@@ -101,7 +101,7 @@ def test_olmoe_prefill_every_expert(mc, olmoe):
     for e in np.nonzero(counts)[0]:           # one token of every expert holding one
         toks.add(int(pt[offsets[e] + counts[e] // 2]))
     hot = int(np.argmax(counts))
-    MT = 128                                  # tokens per m-tile of the grouped GEMMs
+    MT = 64                                   # tokens per m-tile of the grouped GEMMs at this size
     n_mt = (int(counts[hot]) + MT - 1) // MT
     assert n_mt >= 3
     for j in (0, n_mt // 2, n_mt - 1):        # first, middle and last m-tile of the hottest expert

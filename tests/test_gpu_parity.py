@@ -221,8 +221,9 @@ def tiny(mc):
     return L, logical, G
 
 
-# T = 4/5 and 8/9: the down and gate/up kernels switch from 8-wave to 16-wave
-# workgroups there
+# T = 4/5 and 8/9: the down and gate/up GEMVs switch from 8-wave to 16-wave
+# workgroups there; from T = 12 on this layer takes the grouped GEMMs (the GEMVs
+# of larger batches: test_gpu_decode_blocks.py)
 @pytest.mark.parametrize("T", [1, 2, 4, 5, 8, 9, 16, 17, 33, 64, 65, 200])
 def test_forward_tiny_tolerance(mc, tiny, T):
     L, logical, G = tiny
@@ -239,9 +240,8 @@ def test_forward_tiny_tolerance(mc, tiny, T):
 
 @pytest.mark.parametrize("d,T", [(640, 1), (768, 5), (1152, 1), (1152, 16), (1152, 17)])
 def test_forward_split_reduction(mc, d, T):
-    """Batches of at most 16 tokens split the gate/up reduction over d: ragged
-    splits (d = 640: 3 + 2 chunks), an empty last split (d = 1152: 3+3+3+0
-    chunks) and the unsplit path just above (T = 17)."""
+    """Reductions of 5, 6 and 9 chunks, on the GEMVs (whose wave ranges they
+    share out unevenly; T = 1 and 5) and on the grouped GEMMs (T = 16 and 17)."""
     mats, bits, G, logical = layer_case(1, d=d, ffn=384)
     L = pack_gpu(mc, mats, bits, G)
     x = synthetic.activations(1, T, d=d)
@@ -276,14 +276,15 @@ def test_forward_max_tokens_sampled(mc, tiny):
 @pytest.mark.parametrize("cid,E,d,ffn,T,hot", [
     (1, 4, 256, 512, 300, None),      # G = 32, ragged 32-row fragments
     (1, 4, 384, 256, 257, None),      # d not a multiple of the 256-row down tile
-    (1, 4, 256, 512, 600, 1),         # one expert takes every token: 600+ pairs, five 128-token m-tiles
+    (1, 4, 256, 512, 600, 1),         # one expert takes every token: 600+ pairs, 19 m-tiles
     (4, 16, 2048, 1024, 300, None),   # G = 64, 16 experts, top-8, ragged experts
     (1, 4, 256, 384, 300, None),      # ffn = 384: three 128-row gate/up tiles (ffn % 256 = 128)
     (1, 4, 256, 128, 300, None),      # ffn = 128: a single gate/up row tile
 ])
 def test_forward_prefill_shapes(mc, cid, E, d, ffn, T, hot):
-    """Batches above 64 tokens go through the grouped GEMMs: partial 256-token
-    tiles (2, 4, 6, 8 fragment rows), experts with no token, G = 32/64/128."""
+    """Batches above 64 tokens go through the grouped GEMMs: partial m-tiles,
+    experts with no token, G = 32 and 64 (the edges of every m-tile size at every
+    G: test_gpu_small_tiles.py)."""
     c = synthetic.config(cid)
     k = c["k"]
     mats, bits, G, logical = layer_case(cid, E=E, d=d, ffn=ffn)
@@ -306,8 +307,8 @@ def test_forward_prefill_shapes(mc, cid, E, d, ffn, T, hot):
 @pytest.mark.parametrize("ffn", [128, 384])
 @pytest.mark.parametrize("T", [5, 33])
 def test_forward_narrow_ffn_decode(mc, ffn, T):
-    """Decode batches with ffn not a multiple of 256 (one or three 128-row
-    gate/up blocks)."""
+    """Small batches with ffn not a multiple of 256 (one or three 128-row
+    gate/up blocks), on the GEMVs (T = 5) and on the grouped GEMMs (T = 33)."""
     mats, bits, G, logical = layer_case(1, ffn=ffn)
     L = pack_gpu(mc, mats, bits, G)
     x = synthetic.activations(1, T)
@@ -320,8 +321,8 @@ def test_forward_narrow_ffn_decode(mc, ffn, T):
 
 
 def test_forward_skewed_and_dense(mc, tiny):
-    """All tokens on one expert (full token chunks), then tau = 0 with every
-    token protected (dense top-k)."""
+    """All tokens on one expert (full m-tiles), then tau = 0 with every token
+    protected (dense top-k)."""
     L, logical, G = tiny
     T = 64
     x = synthetic.activations(1, T)

@@ -2,10 +2,11 @@
 every index the kernels take from them is range-checked on the device
 (expert ranges, pair blocks, token and position clamps, the prefill set-up's
 capacity check), so the call completes and writes y -- wrong values, but no
-access outside a buffer.  Decode (32 tokens) and the grouped GEMMs (300
-tokens, once with counts too large for the prefill tables and once with
-counts that fit and garbage offsets).  tests/test_route_audit.py checks the
-same index derivations on the CPU."""
+access outside a buffer.  The grouped GEMMs, on a small batch (32 tokens) and
+a larger one (300 tokens), with counts too large for the prefill tables and
+with counts that fit and garbage offsets; tests/test_gpu_decode_blocks.py does
+the same on the decode GEMVs, and tests/test_route_audit.py checks the same
+index derivations on the CPU."""
 import numpy as np
 import pytest
 
