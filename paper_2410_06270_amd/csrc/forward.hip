@@ -222,18 +222,30 @@ static int decode_splits(int K, int* c_per) {
 // the GEMMs most where the routing is even: up to 60 M (20 of 3.1 M, 16 tokens 31.6
 // and 30.7; 24 of 4.9 M 34.2 and 35.5; 17 of 12.6 M 39.9 and 40.4; OLMoE layer, 64 of
 // 6.3 M, 52.5 and 58.4).
-//   A small batch whose GEMM workspace would not fit the library's own scratch
-// keeps the GEMVs.
-static bool gemms_pay(int T, int E, int k, int d, int ffn) {
-  if (T > kDecodeMaxT) return true;
-  const double expert = 3.0 * d * ffn;
-  if ((double)T * k >= (E * expert >= 1.1e9 ? 14.0 : 12.0) * E) return true;
-  return T >= 12 && (T * k < E ? T * k : E) * expert <= (E > 16 ? 60e6 : T < 16 ? 110e6 : 250e6);
+//   Whichever is chosen, mc_moe_forward_noalloc takes what either could take: a
+// small batch whose GEMM workspace would not fit the library's own scratch keeps
+// the GEMVs, and one a little below a line (where the GEMMs lose little) takes
+// the GEMMs if only their workspace fits.
+enum class Gemms { kNo, kNearly, kYes };
+static Gemms gemms_pay(int T, int E, int k, int d, int ffn) {
+  const double expert = 3.0 * d * ffn, touched = (T * k < E ? T * k : E) * expert, pairs = (double)T * k;
+  if (pairs >= (E * expert >= 1.1e9 ? 14.0 : 12.0) * E) return Gemms::kYes;
+  if (T >= 12 && touched <= (E > 16 ? 60e6 : T < 16 ? 110e6 : 250e6)) return Gemms::kYes;
+  return pairs >= 12.0 * E || (T >= 12 && E <= 16 && touched <= 250e6) ? Gemms::kNearly : Gemms::kNo;
 }
 
-static bool use_decode(int T, int E, int k, int d, int ffn) {
-  return !gemms_pay(T, E, k, d, ffn) ||
-         (T <= kDecodeMaxT && prefill_workspace_bytes(T, E, k, d, ffn) > MC_NOALLOC_SCRATCH_BYTES);
+static size_t decode_workspace_bytes(int T, int k, int d, int ffn);
+
+// bytes (may be null): the workspace of the path taken.
+static bool use_decode(int T, int E, int k, int d, int ffn, size_t* bytes = nullptr) {
+  const bool small = T <= kDecodeMaxT;
+  const Gemms gemms = small ? gemms_pay(T, E, k, d, ffn) : Gemms::kYes;
+  const size_t gemm = gemms != Gemms::kNo ? prefill_workspace_bytes(T, E, k, d, ffn) : 0;
+  const size_t gemv = small ? decode_workspace_bytes(T, k, d, ffn) : 0;
+  const bool fits = gemms != Gemms::kNo && gemm <= MC_NOALLOC_SCRATCH_BYTES;
+  const bool decode = small && (!fits || (gemms == Gemms::kNearly && gemv <= MC_NOALLOC_SCRATCH_BYTES));
+  if (bytes) *bytes = decode ? gemv : gemm;
+  return decode;
 }
 
 // Compute units of the current device (one decode workgroup each).
@@ -253,17 +265,19 @@ static int device_cus() {
 // part rounded up to 256 bytes.
 static size_t round256(size_t b) { return ((b + 255) / 256) * 256; }
 
-size_t forward_workspace_bytes(int T, int E, int k, int d, int ffn) {
-  if (gemms_pay(T, E, k, d, ffn)) {   // use_decode, with its workspace at hand
-    const size_t gemm = prefill_workspace_bytes(T, E, k, d, ffn);
-    if (T > kDecodeMaxT || gemm <= MC_NOALLOC_SCRATCH_BYTES) return gemm;
-  }
+static size_t decode_workspace_bytes(int T, int k, int d, int ffn) {
   const size_t P = (size_t)T * k;
   const int ks = decode_splits(d, nullptr);
   const size_t h = round256(P * ffn * sizeof(uint16_t));
   const size_t gu = ks > 1 ? round256((size_t)ks * 2 * P * ffn * sizeof(float)) : 0;
   const size_t part = (size_t)decode_splits(ffn, nullptr) * P * d * sizeof(float);
   return h + gu + part;
+}
+
+size_t forward_workspace_bytes(int T, int E, int k, int d, int ffn) {
+  size_t bytes = 0;
+  (void)use_decode(T, E, k, d, ffn, &bytes);
+  return bytes;
 }
 
 // What the workspace queries answer: enough for T tokens and for every smaller

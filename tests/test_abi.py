@@ -182,6 +182,17 @@ def _timed(f, clock):
     return clock() - t
 
 
+# 12 to 14 pairs an expert: the GEMVs' workspace alone is too large; both fit
+@pytest.mark.parametrize("T,shape", [(24, (16, 8, 7936, 6528)), (27, (16, 8, 7936, 6528)), (49, (8, 2, 8192, 22016)),
+                                     (48, (8, 2, 4096, 14336))])
+def test_scratch_takes_what_either_path_could(lib, T, shape):
+    """A batch near the line between the GEMVs and the GEMMs fits the library's
+    own scratch (32 MiB) wherever one of the two workspaces does."""
+    need = lib["_ZN2mc23forward_workspace_bytesEiiiii"]
+    need.restype, need.argtypes = ctypes.c_size_t, [ctypes.c_int] * 5
+    assert need(T, *shape) <= 32 << 20
+
+
 class _PrefillLayout(ctypes.Structure):
     _fields_ = [(n, ctypes.c_size_t) for n in ("tables", "x", "xsum", "h", "hsum", "part", "total")] + \
                [(n, ctypes.c_int) for n in ("f_max", "mt_max", "nsplit", "tiles")]
